@@ -312,6 +312,22 @@ hmc_status check_ws(const Layout& L, void* ws, size_t bytes) {
   return HMC_OK;
 }
 
+// Bytes of X that the split-precision passes read with the default cache policy (hot_slice in
+// hilo.hip): all of an X that fits the 256 MB memory-side cache beside the passes' other
+// data, and of a larger one a part that stays there while the rest streams past. Measured per
+// gradient, hi + lo planes (p = 1984, K = 10), everything kept / 128 MB kept / nothing kept: X of
+// 220 MB 78 / 81 / 89 us, 260 MB 113 / 111 / 120, 500 MB 205 / 182 / 196, 900 MB 344 / 300 / 312;
+// n = 200000, p = 4096, K = 64 (3.3 GB) with 64 / 96 / 128 / 192 MB kept 1330 / 1329 / 1342 / 1342
+// us, a batch of 1.6 GB 698 / 696 / 710 / 733 us.
+constexpr int64_t kCacheFit = (int64_t)240 << 20, kCacheKeep = (int64_t)96 << 20;
+int64_t plane_bytes(const hmc_problem& pr) { return pr.n * pr.ldx * 2 * (pr.X_lo ? 2 : 1); }
+// Share (of 65536) of a problem's row slices to keep, `bytes` the planes of all the problems of the
+// call. Rows that do not start on 128-byte lines share lines between loads: all kept.
+int32_t hot_share(const hmc_problem& pr, int64_t bytes) {
+  if (bytes <= kCacheFit || pr.ldx % 64 || ((uintptr_t)pr.X | (uintptr_t)pr.X_lo) % 128) return 65536;
+  return (int32_t)(65536.0 * (double)kCacheKeep / (double)bytes);
+}
+
 // Candidate decompositions the autotuner times for a problem (see hmc_autotune).
 std::vector<hmc_tuning> tuning_candidates(const hmc_problem* pr) {
   std::vector<hmc_tuning> out;
@@ -434,6 +450,7 @@ hmc_status gradient_step(const hmc_problem* pr, const Layout& L, const void* Bpo
     h.nsplit = L.hl_nsplit; h.rows_per_split = L.hl_rps;
     h.lpart = at<double>(ws, L.off_lpart);
     h.n = pr->n; h.p = (int32_t)pr->p; h.K = pr->K; h.pin = pr->pin_last_class;
+    h.hot = hot_share(*pr, plane_bytes(*pr));
     HMC_TRY(timed_launch(s, true, [&] {
       return hip_status(launch_hilo(h, L.nb, L.lo, L.hl_logits_wg, L.hl_cols, pack, s), "split-precision pass");
     }));
@@ -648,6 +665,8 @@ hmc_status make_batch_layout(const hmc_problem* probs, int32_t n_prob, int32_t c
   std::stable_sort(B->order.begin(), B->order.end(),
                    [&](int32_t u, int32_t v) { return probs[u].p > probs[v].p; });
   for (auto& f : B->first) f.assign(n_prob + 1, 0);
+  int64_t bytes = 0, slices = 0;
+  for (int b = 0; b < n_prob; ++b) bytes += plane_bytes(probs[b]);
   size_t off = 0;
   B->off_table = off; off = align_up(off + sizeof(BatchProb) * n_prob);
   B->off_first = off; off = align_up(off + 5 * sizeof(int32_t) * (n_prob + 1));
@@ -666,6 +685,9 @@ hmc_status make_batch_layout(const hmc_problem* probs, int32_t n_prob, int32_t c
     P.gcols = (int32_t)((pr.p + 127) / 128);
     P.rps = rows;
     P.nsplit = (int32_t)((pr.n + rows - 1) / rows);
+    P.hot = hot_share(pr, bytes);
+    P.slice0 = (int32_t)slices;
+    slices += P.nsplit;
     P.cstride = (pk + 63) / 64 * 64;
     P.gstride = chains * P.cstride;
     P.ne = (int32_t)((pk + 63) / 64);

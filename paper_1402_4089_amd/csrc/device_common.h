@@ -88,6 +88,7 @@ constexpr int kWaitLgkm0 = 0xC07F;   // lgkmcnt(0)
 // vmcnt(n): wait until at most n vector memory operations of this wave are in flight.
 constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kHalfMirror = 0x141, kRowMirror = 0x140;
+constexpr int kRowBcast = 0x150;     // + l: lane l of each row of 16 to the whole row
 
 // Reductions over the 16 lanes of a DPP row. Each stage combines a lane with a partner
 // through a symmetric operation, so every lane ends with the bitwise-identical result.
@@ -102,6 +103,40 @@ template <typename T> __device__ __forceinline__ T sum16(T v) {
   v += dpp<kQuadXor2>(v);
   v += dpp<kHalfMirror>(v);
   return v + dpp<kRowMirror>(v);
+}
+
+// Sums over the 16 lanes of a DPP row of N values per lane (N = 4, 8 or 16), one sum per lane
+// instead of every sum in every lane: at each of the first log2 N stages a lane passes half of
+// its values to its partner and adds the partner's half, 2 N - 2 exchanges in all where
+// sum16 takes 4 N. The same pairs are added as in sum16, so the sums have its bits. With l the
+// lane's index in its row (bits l0 .. l3), the lane ends with the sum of value row_sum_index
+// mod N, whose bits are l0 ^ l2, l1 ^ l2, l2 ^ l3, l3: partners of a stage (l ^ 1, l ^ 2,
+// 7 - l, 15 - l) differ in that stage's bit and agree in the earlier ones.
+__device__ __forceinline__ int row_sum_index(int l) {
+  return (l & 8) | ((l ^ (l >> 1)) & 4) | ((l ^ (l >> 1)) & 2) | ((l ^ (l >> 2)) & 1);
+}
+// The lane of a row that holds value v's sum (its lowest, where several do).
+constexpr int row_sum_lane(int v) {
+  const int l3 = v >> 3 & 1, l2 = (v >> 2 & 1) ^ l3, l1 = (v >> 1 & 1) ^ l2, l0 = (v & 1) ^ l2;
+  return l3 * 8 + l2 * 4 + l1 * 2 + l0;
+}
+template <int CTRL, int N> __device__ __forceinline__ void row_sum_stage(double (&v)[16], bool odd) {
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) {
+    const double a = v[2 * i], b = v[2 * i + 1];
+    v[i] = (odd ? b : a) + dpp<CTRL>(odd ? a : b);
+  }
+}
+template <int N> __device__ __forceinline__ double row_sums(double (&v)[16]) {
+  static_assert(N == 4 || N == 8 || N == 16, "two to four exchanging stages");
+  const int b = row_sum_index(threadIdx.x & 15);
+  row_sum_stage<kQuadXor1, N>(v, b & 1);
+  row_sum_stage<kQuadXor2, N / 2>(v, b & 2);
+  if constexpr (N >= 8) row_sum_stage<kHalfMirror, N / 4>(v, b & 4);
+  else v[0] += dpp<kHalfMirror>(v[0]);
+  if constexpr (N >= 16) row_sum_stage<kRowMirror, N / 8>(v, b & 8);
+  else v[0] += dpp<kRowMirror>(v[0]);
+  return v[0];
 }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint64_t bytes) {
@@ -159,13 +194,16 @@ __device__ __forceinline__ double philox_uniform(uint64_t seed, int chain, int64
   return u53(c[0], c[1]);
 }
 
-// bfloat16 of a float, rounded to nearest even.
-__device__ __forceinline__ uint16_t bf16_from_f32(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// bfloat16 of two floats, rounded to nearest even, the first in the low half: one
+// v_cvt_pk_bf16_f32, whose result is that of adding 0x7FFF plus the last kept bit to the
+// encoding (a NaN: its upper half made quiet) for every one of the 2^32 inputs, subnormals
+// included.
+__device__ __forceinline__ uint32_t bf16x2_from_f32(float a, float b) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
 }
+__device__ __forceinline__ uint16_t bf16_from_f32(float f) { return (uint16_t)bf16x2_from_f32(f, f); }
 __device__ __forceinline__ float f32_from_bf16(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // Packed B operand of the split-precision contractions: for NB blocks of 16 classes, the

@@ -11,6 +11,8 @@
 // X^T R over a slice of rows each, and the shared epilogue sums the slices.
 #include <math.h>
 
+#include <utility>
+
 #include "device_common.h"
 
 namespace hmcx {
@@ -40,6 +42,15 @@ __device__ __forceinline__ u16 bf16_from_f64(double x) {
 __device__ __forceinline__ uint32_t pack2(u16 a, u16 b) { return (uint32_t)a | ((uint32_t)b << 16); }
 
 __device__ __forceinline__ bf16x8 as_frag(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+// Two transposing reads of 4 rows x 16 columns (per 16-lane group) as the 8 elements of an operand.
+__device__ __forceinline__ u32x4 tr_pair(const u16* a, const u16* b) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  const uint2 u = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)a));
+  const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)b));
+  return u32x4{u.x, u.y, v.x, v.y};
+}
 
 __device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -131,6 +142,16 @@ struct Job {
   int pin;                 // 1: column K-1 of B is packed as zero (beta_K = 0)
 };
 
+// Cache policy of the loads of X (the aux operand of a buffer load): some row slices (as many
+// as fit the memory-side cache, spread evenly over X so that its bandwidth and the memory's
+// add up) are read with the default policy and found there again by the other pass, the rest
+// with the non-temporal hint, which streams faster and leaves the cached part alone. The X
+// loads of both passes use whole 128-byte lines.
+constexpr int kKeep = 0, kStream = 2;
+__device__ __forceinline__ bool hot_slice(int64_t s, int share) {
+  return (int)((uint32_t)s * (uint32_t)share & 0xFFFFu) < share;
+}
+
 // B -> packed hi/lo operand in the lane order of the MFMA B input: fragment (k-step s,
 // class block nb, plane) holds, for lane l, the 8 values B[32 s + 8 (l / 16) + j][class
 // 16 nb + l % 16 of the block's group], j = 0..7. Padding rows and classes are zero.
@@ -158,24 +179,44 @@ __device__ __forceinline__ void pack_b_body(const Job& j, int64_t t) {
 // Logits, softmax and packed residuals of row block rb (kHiloRows rows); every thread
 // of the workgroup takes part (barriers inside).
 //
-// Wave w owns kHiloMB 16-row M blocks and all 16*NB padded classes. Its X operand
-// comes straight from global memory, kBChunk - 1 k steps ahead of the MFMAs: lane l
-// loads the 8 consecutive columns 32 s + 8 (l / 16) .. of row l % 16 of each M block,
-// the A input layout of the MFMA. The packed B operand, shared by all waves, is staged in
-// LDS (`bs`, two buffers of kBChunk k steps) one chunk ahead. After the k loop, lane l
-// holds logits of rows 4 (l / 16) + i (i < 4) for class 16 nb + l % 16, so every row is
-// spread over one 16-lane DPP row: max and sum are DPP reductions (across the GROUP
+// Reading X bounds this: 2 or 4 bytes per element once, the matrix cores are busy a quarter
+// of that time. Wave w owns kHiloMB 16-row M blocks and all 16*NB padded classes. The MFMA A
+// operand wants, of each 32-column k step, 8 consecutive columns of row l % 16 in lane l, but
+// loads of that shape (16 rows x 64 bytes per instruction, the four lanes of a row 16 lanes
+// apart) stream at 4.2 TB/s (n = 200000, p = 4096). X is therefore read in chunks of 64
+// columns, 8 rows x 128 bytes (whole lines) per instruction, kXDepth chunks ahead in registers, and each chunk goes through a piece of LDS that only its wave touches:
+// stored by rows, read back as operands, the 16-byte pieces of a row XOR-ed with (row / 2) % 8
+// so that both accesses are free of bank conflicts. The packed B operand, shared by all
+// waves, is staged in LDS (`bs`, two buffers of kBSteps k steps) one chunk ahead. After the k
+// loop, lane l holds logits of rows 4 (l / 16) + i (i < 4) for class 16 nb + l % 16, so every
+// row is spread over one 16-lane DPP row: max and sum are DPP reductions (across the GROUP
 // blocks of a softmax group in-lane). The residual R = onehot(y) - P is split into bf16
 // hi/lo and stored in the B-input lane order of the gradient kernel. lacc[group] gains
 // this wave's log-likelihood terms (in the lane holding each row's label).
-constexpr int kBChunk = 4;                       // k steps of B per LDS buffer
-template <int NB> constexpr int bchunk_elems() { return kBChunk * NB * 1024; }
+//
+// LDS per workgroup: X 16 KB a plane and B 32 KB (16 KB for one class block), so that two
+// workgroups share a compute unit; the X registers of kXDepth chunks are 64 either way.
+template <int NB> constexpr int kBSteps = NB == 4 ? 2 : 4;         // k steps of B per LDS buffer
+template <bool LO> constexpr int kXDepth = LO ? 2 : 4;             // 64-column chunks of X in flight
+template <int NB> constexpr int bchunk_elems() { return kBSteps<NB> * NB * 1024; }
+template <int NB, bool LO> constexpr int logits_lds_elems() {
+  return 2 * bchunk_elems<NB>() + (LO ? 2 : 1) * kHiloRows * 64;
+}
+
+// lse[v] = zmx[v] + the log held by the lane of the row that has sum v.
+template <int F, int... V>
+__device__ __forceinline__ void read_logs(double lg, const float (&zmx)[F], double (&lse)[F],
+                                          std::integer_sequence<int, V...>) {
+  ((lse[V] = (double)zmx[V] + dpp<kRowBcast + row_sum_lane(V)>(lg)), ...);
+}
 
 // Softmax over the K valid classes of each row and group of row block rb, FP64 statistics,
-// and the packed residuals. After the 16-lane reductions every lane of a row holds the sums
-// of exponentials of its 4 rows x NG groups; the FP64 log is taken once per (row, group) —
-// lane m of the row takes sum number m — and read back by the lanes that need it with a
-// shuffle. lacc[group] gains this wave's log-likelihood terms (in the label's lane).
+// and the packed residuals. The sums of exponentials of a lane's 4 rows x NG groups are formed
+// one per lane (row_sums), where the FP64 log is taken, and read back from that lane by the
+// others of the row. lacc[group] gains this wave's log-likelihood terms (in the label's lane).
+// Vector work bounds it (no other kernel of the pass overlaps it within the workgroup): per
+// pair of elements two exponentials each, three FP64 operations and the two packed
+// conversions of the residual's planes.
 template <int NB, int GROUP>
 __device__ __forceinline__ void softmax_residuals(const Job& j, int64_t rb,
                                                   const f32x4 (&acc)[kHiloMB][NB],
@@ -189,13 +230,11 @@ __device__ __forceinline__ void softmax_residuals(const Job& j, int64_t rb,
   const int K = j.K;
   const int64_t r0 = rb * kHiloRows + (int64_t)w * 16 * MB;
   constexpr int F = 4 * NG;
-  static_assert(F <= 16, "one log per lane per M block");
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     const int64_t rblk = r0 / 32 + mb / 2;     // 32-row block of the gradient kernel
-    uint32_t rh[NB][2], rl[NB][2];
-    float zmx[4][NG];
-    double ssum[4][NG];
+    float zmx[F];
+    double ssum[16];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -209,42 +248,30 @@ __device__ __forceinline__ void softmax_residuals(const Job& j, int64_t rb,
 #pragma unroll
         for (int b = 0; b < GROUP; ++b)
           if (16 * b + m < K) s += (double)dev_exp(acc[mb][q * GROUP + b][i] - zmax);
-        zmx[i][q] = zmax;
-        ssum[i][q] = sum16(s);
+        zmx[i * NG + q] = zmax;
+        ssum[i * NG + q] = s;
       }
-    double v = 1.0;
+    const double lg = log(row_sums<F>(ssum));
+    double lse[F];
+    read_logs<F>(lg, zmx, lse, std::make_integer_sequence<int, F>{});
+    uint32_t rh[NB][2], rl[NB][2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int nb = 0; nb < NB; ++nb) {
+      const int q = nb / GROUP, kk = 16 * (nb % GROUP) + m;
+      float r[4];
 #pragma unroll
-      for (int q = 0; q < NG; ++q) v = (i * NG + q == m) ? ssum[i][q] : v;
-    const double lg = log(v);
+      for (int i = 0; i < 4; ++i) {
+        const bool valid = r0 + 16 * mb + 4 * g + i < n && kk < K;
+        const bool hit = valid && kk == ylab[mb][i];
+        const double zl = (double)acc[mb][nb][i] - lse[i * NG + q];   // log softmax
+        lacc[q] += hit ? zl : 0.0;                                    // the label's lane only
+        r[i] = valid ? (hit ? 1.0f : 0.0f) - dev_exp((float)zl) : 0.0f;
+      }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t row = r0 + 16 * mb + 4 * g + i;
-      const bool valid = row < n;
-      const int yi = valid ? ylab[mb][i] : -1;
-#pragma unroll
-      for (int q = 0; q < NG; ++q) {
-        const double lse = (double)zmx[i][q] + __shfl(lg, (lane & 48) | (i * NG + q), 64);
-#pragma unroll
-        for (int b = 0; b < GROUP; ++b) {
-          const int kk = 16 * b + m, nb = q * GROUP + b;
-          float r = 0.0f;
-          if (valid && kk < K) {
-            const double zl = (double)acc[mb][nb][i] - lse;     // log softmax
-            if (kk == yi) lacc[q] += zl;                        // the label's lane only
-            r = (kk == yi ? 1.0f : 0.0f) - dev_exp((float)zl);
-          }
-          const u16 h = bf16_from_f32(r);
-          const u16 l = bf16_from_f32(r - f32_from_bf16(h));
-          if (i & 1) {
-            rh[nb][i >> 1] |= (uint32_t)h << 16;
-            rl[nb][i >> 1] |= (uint32_t)l << 16;
-          } else {
-            rh[nb][i >> 1] = h;
-            rl[nb][i >> 1] = l;
-          }
-        }
+      for (int h = 0; h < 2; ++h) {
+        rh[nb][h] = bf16x2_from_f32(r[2 * h], r[2 * h + 1]);
+        rl[nb][h] = bf16x2_from_f32(r[2 * h] - __uint_as_float(rh[nb][h] << 16),
+                                    r[2 * h + 1] - __uint_as_float(rh[nb][h] & 0xFFFF0000u));
       }
     }
     // rows 16 (mb % 2) + 4 g + i of this 32-row block sit in lane 16 (2 (mb % 2) + g / 2)
@@ -259,34 +286,37 @@ __device__ __forceinline__ void softmax_residuals(const Job& j, int64_t rb,
   }
 }
 
-template <int NB, int GROUP, bool LO>
+template <int NB, int GROUP, bool LO, int AUX>
 __device__ __forceinline__ void logits_rows(const Job& j, int64_t rb, double (&lacc)[NB / GROUP],
                                             u16* __restrict__ bs) {
-  constexpr int CH = bchunk_elems<NB>();         // u16 per chunk (hi and lo fragments)
+  constexpr int PL = LO ? 2 : 1;
+  constexpr int BST = kBSteps<NB>, XD = kXDepth<LO>;
+  constexpr int CH = bchunk_elems<NB>();         // u16 per B chunk (hi and lo fragments)
   constexpr int PER = CH / 8 / (kHiloWaves * 64);   // 16-byte pieces per thread per chunk
   static_assert(CH / 8 % (kHiloWaves * 64) == 0, "a B chunk is a whole number of 16-byte pieces per thread");
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = lane & 15, g = lane >> 4;
   const int64_t n = j.n;
   const int p = j.p;
-  const int nks = (p + 31) / 32;
+  const int nks = (p + 31) / 32, nxc = (nks + 1) / 2;   // k steps, 64-column chunks
   constexpr int MB = kHiloMB;
   f32x4 acc[MB][NB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // X fragments come from branch-free buffer loads whose resource starts at the row
-  // block and ends at row n, so rows past n read as zero; columns past p are zeroed in
-  // registers on the last (ragged) k step. Offsets fit 32 bits (ldx < 2^23).
+  // X comes from branch-free buffer loads whose resource starts at the row block and ends at
+  // row n, so rows past n read as zero. Offsets fit 32 bits (ldx < 2^23). Instruction i loads
+  // rows 8 i + lane / 8 of the wave's 32, 16-byte piece lane % 8 of the chunk.
   const int64_t rbase = rb * kHiloRows;
   const uint64_t rem = (uint64_t)(n - rbase) * j.ldx * 2;
   const __amdgpu_buffer_rsrc_t rh = make_rsrc(j.Xhi + rbase * j.ldx, rem);
   const __amdgpu_buffer_rsrc_t rl = make_rsrc(LO ? j.Xlo + rbase * j.ldx : j.Xhi, LO ? rem : 0);
-  uint32_t xoff[MB];
+  const int piece = lane & 7;
+  uint32_t xoff[4];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-    xoff[mb] = (uint32_t)(((int64_t)(w * 16 * MB + 16 * mb + m) * j.ldx + 8 * g) * 2);
+  for (int i = 0; i < 4; ++i)
+    xoff[i] = (uint32_t)(((int64_t)(w * 32 + 8 * i + (lane >> 3)) * j.ldx + 8 * piece) * 2);
   // labels of this lane's rows, loaded now so their latency hides behind the k loop
   // (rows past n read as zero and are not used)
   const __amdgpu_buffer_rsrc_t yres = make_rsrc(j.y + rbase, (uint64_t)(n - rbase) * 4);
@@ -297,7 +327,7 @@ __device__ __forceinline__ void logits_rows(const Job& j, int64_t rb, double (&l
     for (int i = 0; i < 4; ++i)
       ylab[mb][i] = __builtin_amdgcn_raw_buffer_load_b32(
           yres, (int)((w * 16 * MB + 16 * mb + 4 * g + i) * 4), 0, 0);
-  const int nch = (nks + kBChunk - 1) / kBChunk;
+  const int nch = (nks + BST - 1) / BST;
   const int64_t bp_total = (int64_t)nks * NB * 1024;
   u32x4 bst[PER];
   // every load below is issued unconditionally: buffer loads past a resource's end read
@@ -317,70 +347,105 @@ __device__ __forceinline__ void logits_rows(const Job& j, int64_t rb, double (&l
       *reinterpret_cast<u32x4*>(bs + buf * CH + (i * kHiloWaves * 64 + threadIdx.x) * 8) = bst[i];
   };
 
-  // A fragments of k step ks. A step at or past nks (the ring's refills during the last
-  // chunk) would read the next rows' bytes, real traffic that is thrown away: those loads
-  // take an empty resource instead (still issued, so the issue stays branch-free).
-  const __amdgpu_buffer_rsrc_t rz = make_rsrc(j.Xhi, 0);
-  auto load_a = [&](int ks, u32x4 (&ah)[MB], u32x4 (&al)[MB]) {
-    const bool live = ks < nks;
+  // X chunk xc of this wave's rows. A piece at or past column p (and a chunk past the last)
+  // would read the row's padding or the next rows' bytes, real traffic that is thrown away:
+  // its offset is put past every resource's end, so it reads zero and moves nothing.
+  struct XRegs { u32x4 v[4][PL]; };
+  auto load_x = [&](int xc, XRegs& x) {
+    const bool live = 64 * xc + 8 * piece < p;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      ah[mb] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(live ? rh : rz, (int)(xoff[mb] + 64 * ks), 0, 0));
-      if (LO) al[mb] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(live ? rl : rz, (int)(xoff[mb] + 64 * ks), 0, 0));
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t off = live ? xoff[i] + 128 * (uint32_t)xc : 0xFFFFFFF0u;
+      x.v[i][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rh, (int)off, 0, AUX));
+      if (LO) x.v[i][PL - 1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rl, (int)off, 0, AUX));
     }
   };
-  // zero the elements of this lane's 8 columns 32 ks + 8 g .. that lie past p
-  auto mask_tail = [&](int ks, u32x4 (&ah)[MB], u32x4 (&al)[MB]) {
-    const int lim = p - (32 * ks + 8 * g);
+  // zero the elements of this lane's 8 columns 64 xc + 8 piece .. that lie past p
+  auto mask_tail = [&](int xc, XRegs& x) {
+    const int lim = p - (64 * xc + 8 * piece);
     u32x4 mk;
 #pragma unroll
     for (int d = 0; d < 4; ++d)
       mk[d] = (2 * d < lim ? 0x0000FFFFu : 0u) | (2 * d + 1 < lim ? 0xFFFF0000u : 0u);
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      ah[mb] &= mk;
-      if (LO) al[mb] &= mk;
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int pl = 0; pl < PL; ++pl) x.v[i][pl] &= mk;
+  };
+  u16* xw = bs + 2 * CH + w * PL * 2048;          // this wave's 32 rows x 64 columns of each plane
+  const int xput = (lane >> 3) * 64;              // row lane / 8 of instruction 0
+  auto stash_x = [&](const XRegs& x) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int pos = piece ^ ((4 * i + (lane >> 4)) & 7);
+#pragma unroll
+      for (int pl = 0; pl < PL; ++pl)
+        *reinterpret_cast<u32x4*>(xw + pl * 2048 + xput + i * 512 + 8 * pos) = x.v[i][pl];
     }
   };
-  // X fragments kBChunk k steps ahead in a ring of kBChunk register sets: set kk holds
-  // step ks = c kBChunk + kk of chunk c and is reloaded with step ks + kBChunk right after
-  // its MFMAs, so kBChunk - 1 steps of loads stay in flight per wave while one is used.
-  // The ring index is static in the unrolled chunk, so no register is copied (a copy of a
-  // register a load has not yet filled would wait for that load).
-  u32x4 xh[kBChunk][MB], xl[kBChunk][MB];
+  // k step 2 xc + h of the staged chunk with fragment kk of the B buffer
+  auto step = [&](int h, const u16* bk) {
+    bf16x8 bh[NB], bl[NB], ah[MB], al[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const u16* f = xw + (16 * mb + m) * 64 + 8 * ((4 * h + g) ^ ((m >> 1) & 7));
+      ah[mb] = as_frag(*reinterpret_cast<const u32x4*>(f));
+      if (LO) al[mb] = as_frag(*reinterpret_cast<const u32x4*>(f + 2048));
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      bh[nb] = as_frag(*reinterpret_cast<const u32x4*>(bk + nb * 1024));
+      bl[nb] = as_frag(*reinterpret_cast<const u32x4*>(bk + nb * 1024 + 512));
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mma(ah[mb], bh[nb], acc[mb][nb]);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mma(ah[mb], bl[nb], acc[mb][nb]);
+    if (LO) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mma(al[mb], bh[nb], acc[mb][nb]);
+    }
+  };
+  // Register set q holds chunks q, q + kXDepth, ...; it is reloaded right after its chunk is
+  // stored to LDS, so kXDepth - 1 chunks of loads stay in flight per wave and one more is
+  // issued while a chunk is used. The index is static in the unrolled loop, so no register is
+  // copied (a copy of a register a load has not yet filled would wait for that load).
+  constexpr int XB = BST / 2;                     // X chunks per B chunk
+  constexpr int UN = XD > XB ? XD / XB : 1;       // B chunks per turn of the register ring
+  XRegs x[XD];
   fetch_b(0);
   stash_b(0);
 #pragma unroll
-  for (int kk = 0; kk < kBChunk; ++kk) load_a(kk, xh[kk], xl[kk]);
+  for (int q = 0; q < XD; ++q) load_x(q, x[q]);
   __syncthreads();
-  for (int c = 0; c < nch; ++c) {
-    fetch_b(c + 1);
-    const u16* bc = bs + (c & 1) * CH + lane * 8;
+  for (int c0 = 0; c0 < nch; c0 += UN) {
 #pragma unroll
-    for (int kk = 0; kk < kBChunk; ++kk) {
-      const int ks = c * kBChunk + kk;
-      if (ks == nks - 1 && (p & 31)) mask_tail(ks, xh[kk], xl[kk]);
-      bf16x8 bh[NB], bl[NB];
+    for (int u = 0; u < UN; ++u) {
+      const int c = c0 + u;
+      if (c >= nch) break;
+      fetch_b(c + 1);
+      const u16* bc = bs + (c & 1) * CH + lane * 8;
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const u16* f = bc + (kk * NB + nb) * 1024;
-        bh[nb] = as_frag(*reinterpret_cast<const u32x4*>(f));
-        bl[nb] = as_frag(*reinterpret_cast<const u32x4*>(f + 512));
+      for (int b = 0; b < XB; ++b) {
+        const int xc = c * XB + b;
+        XRegs& xr = x[(u * XB + b) % XD];
+        if (xc == nxc - 1 && (p & 7)) mask_tail(xc, xr);
+        __builtin_amdgcn_wave_barrier();          // the previous chunk's operands are read
+        stash_x(xr);
+        load_x(xc + XD, xr);
+        __builtin_amdgcn_wave_barrier();
+        if (2 * xc < nks) step(0, bc + (2 * b) * NB * 1024);
+        if (2 * xc + 1 < nks) step(1, bc + (2 * b + 1) * NB * 1024);
       }
-      if (ks < nks) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) {
-            acc[mb][nb] = mma(as_frag(xh[kk][mb]), bh[nb], acc[mb][nb]);
-            acc[mb][nb] = mma(as_frag(xh[kk][mb]), bl[nb], acc[mb][nb]);
-            if (LO) acc[mb][nb] = mma(as_frag(xl[kk][mb]), bh[nb], acc[mb][nb]);
-          }
-      }
-      load_a(ks + kBChunk, xh[kk], xl[kk]);
+      stash_b((c + 1) & 1);
+      __syncthreads();
     }
-    stash_b((c + 1) & 1);
-    __syncthreads();
   }
 
   softmax_residuals<NB, GROUP>(j, rb, acc, ylab, lacc);
@@ -394,17 +459,19 @@ __device__ __forceinline__ void logits_rows(const Job& j, int64_t rb, double (&l
 // fragments) are loaded into registers two stages ahead of the math and stored to one of
 // two LDS buffers one stage ahead, so two stages of loads stay in flight per workgroup.
 // Wave w owns columns 32 w .. 32 w + 31 (two 16-column M blocks); the MFMA A input wants,
-// per lane, 8 consecutive ROWS of one column, gathered from LDS with 16-bit reads. The
-// 16-byte chunks of a staged row are XOR-swizzled by 2 ((row / 8) % 4) so that the four
-// 8-row groups read at once fall in different banks. Rows outside the slice and columns
-// past p load as zero.
+// per lane, 8 consecutive ROWS of one column: two transposing LDS reads (ds_read_b64_tr_b16,
+// each turning 4 rows x 16 columns of a 16-lane group) per operand, in place of eight 16-bit
+// reads and their packing, which with the residual reads had filled the LDS pipe for most of
+// the time that streaming a stage takes. The 16-byte chunks of a staged row are XOR-swizzled
+// by 2 (row % 4 + 4 ((row / 8) % 2)), so that the eight rows a read touches at once fall in
+// different banks. Rows outside the slice and columns past p load as zero.
 template <int NB, bool LO> constexpr int grad_stage_elems() { return (LO ? 2 : 1) * 4096 + NB * 1024; }
 template <int NB> struct RPiece;                    // residual u16 per thread and stage
 template <> struct RPiece<1> { typedef uint2 type; static constexpr int N = 4; };
 template <> struct RPiece<2> { typedef u32x4 type; static constexpr int N = 8; };
 template <> struct RPiece<4> { typedef u32x4 type; static constexpr int N = 8; };
 
-template <int NB, int GROUP, bool LO>
+template <int NB, int GROUP, bool LO, int AUX>
 __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg, int64_t rend,
                                           float* __restrict__ gp, int64_t cstride,
                                           u16* __restrict__ xs) {
@@ -447,13 +514,9 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
 #pragma unroll
     for (int pl = 0; pl < PL; ++pl) {
       const __amdgpu_buffer_rsrc_t xr = make_rsrc((pl ? j.Xlo : j.Xhi) + xbase, xbytes);
-      // X is read once here and its lines are used whole by this load: the non-temporal hint
-      // (aux bit 1) lets the L2 evict them first, so the packed residual rows that the slice's
-      // other column blocks re-read stay cached (measured: n=200000, p=4096 gradient pass
-      // 1360 -> 1320 us; batched update 3535 -> 3465 us)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        R.x[h][pl] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)xo[h], 0, 2));
+        R.x[h][pl] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)xo[h], 0, AUX));
     }
     const uint32_t roff = (uint32_t)((real ? row0 / 32 : (int64_t)(rpk_bytes / (NB * 2048))) * NB * 2048);
 #pragma unroll
@@ -469,7 +532,7 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int q = sr + 16 * h;
-      const int pos = sc ^ (2 * ((q >> 3) & 3));
+      const int pos = sc ^ (2 * ((q & 3) | ((q >> 1) & 4)));
 #pragma unroll
       for (int pl = 0; pl < PL; ++pl)
         *reinterpret_cast<u32x4*>(buf + pl * 4096 + q * 128 + 8 * pos) = R.x[h][pl];
@@ -485,6 +548,13 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  // transposing reads: lane 16 g + m supplies row 8 g + m / 4 (+ 4), columns 4 (m % 4) .. + 3 of
+  // the M block, and receives column m of rows 8 g .. 8 g + 3 (+ 4)
+  const int trow = 8 * g + (m >> 2);
+  int tcol[2];
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb)
+    tcol[mb] = 8 * ((4 * w + 2 * mb + ((m >> 1) & 1)) ^ (2 * ((m >> 2) | (4 * (g & 1))))) + 4 * (m & 1);
   auto compute = [&](const u16* cur) {
     bf16x8 bh[NB], bl[NB];
 #pragma unroll
@@ -494,16 +564,11 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
     }
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
-      const int cl = 32 * w + 16 * mb + m;
-      const int off = ((cl >> 3) ^ (2 * g)) * 8 + (cl & 7);
       bf16x8 af[PL];
 #pragma unroll
       for (int pl = 0; pl < PL; ++pl) {
-        const u16* t = cur + pl * 4096;
-        u16 v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = t[(8 * g + e) * 128 + off];
-        af[pl] = as_frag(u32x4{pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7])});
+        const u16* t = cur + pl * 4096 + trow * 128 + tcol[mb];
+        af[pl] = as_frag(tr_pair(t, t + 4 * 128));
       }
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
@@ -574,11 +639,14 @@ template <int NB, bool LO>
 __global__ __launch_bounds__(kHiloWaves * 64) void hilo_logits(HiloArgs a) {
   constexpr int ROWS = kHiloRows;
   __shared__ double lsum[kHiloWaves];
-  __shared__ __attribute__((aligned(16))) u16 bs[2 * bchunk_elems<NB>()];
+  __shared__ __attribute__((aligned(16))) u16 bs[logits_lds_elems<NB, LO>()];
   const Job j = job_of(a);
   const int64_t nrb = (a.n + ROWS - 1) / ROWS;
   double lacc[1] = {0.0};
-  for (int64_t rb = blockIdx.x; rb < nrb; rb += gridDim.x) logits_rows<NB, NB, LO>(j, rb, lacc, bs);
+  for (int64_t rb = blockIdx.x; rb < nrb; rb += gridDim.x) {
+    if (hot_slice(rb * ROWS / a.rows_per_split, a.hot)) logits_rows<NB, NB, LO, kKeep>(j, rb, lacc, bs);
+    else logits_rows<NB, NB, LO, kStream>(j, rb, lacc, bs);
+  }
   const double v = wave_sum(lacc[0]);
   if ((threadIdx.x & 63) == 0) lsum[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -600,7 +668,8 @@ __global__ __launch_bounds__(256) void hilo_grad(HiloArgs a, int gcols) {
   const int64_t cb = it % gcols, sl = it / gcols;
   const int64_t rbeg = sl * a.rows_per_split;
   const int64_t rend = rbeg + a.rows_per_split < a.n ? rbeg + a.rows_per_split : a.n;
-  grad_cols<NB, NB, LO>(job_of(a), cb * 128, rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
+  if (hot_slice(sl, a.hot)) grad_cols<NB, NB, LO, kKeep>(job_of(a), cb * 128, rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
+  else grad_cols<NB, NB, LO, kStream>(job_of(a), cb * 128, rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -635,7 +704,7 @@ template <int NB, int GROUP, bool LO>
 __global__ __launch_bounds__(kHiloWaves * 64, 2) void batch_logits(BatchArgs a) {
   constexpr int NC = NB / GROUP;                  // chains
   __shared__ double lsum[kHiloWaves][NC];
-  __shared__ __attribute__((aligned(16))) u16 bs[2 * bchunk_elems<NB>()];
+  __shared__ __attribute__((aligned(16))) u16 bs[logits_lds_elems<NB, LO>()];
   const int64_t total = a.first_logits[a.nprob];
   for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
     const int b = find_problem(a.first_logits, a.nprob, it);
@@ -644,7 +713,9 @@ __global__ __launch_bounds__(kHiloWaves * 64, 2) void batch_logits(BatchArgs a) 
     double lacc[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) lacc[c] = 0.0;
-    logits_rows<NB, GROUP, LO>(job_of(P, a.at_current ? P.B : P.Bp), rb, lacc, bs);
+    const Job j = job_of(P, a.at_current ? P.B : P.Bp);
+    if (hot_slice(P.slice0 + rb * kHiloRows / P.rps, P.hot)) logits_rows<NB, GROUP, LO, kKeep>(j, rb, lacc, bs);
+    else logits_rows<NB, GROUP, LO, kStream>(j, rb, lacc, bs);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const double v = wave_sum(lacc[c]);
@@ -674,8 +745,10 @@ __global__ __launch_bounds__(256) void batch_grad(BatchArgs a) {
     const int64_t cb = k % P.gcols, s = k / P.gcols;
     const int64_t rbeg = s * P.rps;
     const int64_t rend = rbeg + P.rps < P.n ? rbeg + P.rps : P.n;
-    grad_cols<NB, GROUP, LO>(job_of(P, a.at_current ? P.B : P.Bp), cb * 128, rbeg, rend,
-                         P.gpart + s * P.gstride, P.cstride, xs);
+    const Job j = job_of(P, a.at_current ? P.B : P.Bp);
+    float* gp = P.gpart + s * P.gstride;
+    if (hot_slice(P.slice0 + s, P.hot)) grad_cols<NB, GROUP, LO, kKeep>(j, cb * 128, rbeg, rend, gp, P.cstride, xs);
+    else grad_cols<NB, GROUP, LO, kStream>(j, cb * 128, rbeg, rend, gp, P.cstride, xs);
   }
 }
 

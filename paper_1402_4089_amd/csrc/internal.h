@@ -147,6 +147,7 @@ struct HiloArgs {
   int64_t n;
   int32_t p, K;
   int32_t pin;          // 1: column K-1 of B is packed as zero
+  int32_t hot;          // share of the row slices kept in the memory-side cache, of 65536
 };
 
 // One problem of a batch (device table entry). Each problem runs `chains` chains that
@@ -167,6 +168,8 @@ struct BatchProb {
   float* gpart;             // [nsplit][chains][cstride]
   int64_t gstride, cstride; // cstride = p K rounded up to 64; gstride = chains * cstride
   int32_t nsplit, gcols;
+  int32_t hot;              // share of the row slices kept in the memory-side cache, of 65536
+  int32_t slice0;           // slices of the entries before this one
   int64_t rps;              // rows per gradient slice (a multiple of 32)
   int32_t nrb;              // logits row blocks of kHiloRows rows
   double* lpart;            // [nrb][chains]

@@ -37,39 +37,36 @@ constexpr int group_steps(int w) { return w <= 2 ? 16 : w <= 4 ? 8 : w <= 10 ? 4
 // pieces, so that the 16 rows of a read fall in different banks.
 constexpr int64_t tile_pitch(int64_t p, size_t ts) { return (p + 63) / 64 * 64 + 16 / (int64_t)ts; }
 
-template <typename T>
-__device__ __forceinline__ T buf1(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t s);
-template <>
-__device__ __forceinline__ float buf1<float>(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t s) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, (int)s, 0));
+template <typename T> __device__ __forceinline__ T buf1(__amdgpu_buffer_rsrc_t r, uint32_t off);
+template <> __device__ __forceinline__ float buf1<float>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
-template <>
-__device__ __forceinline__ double buf1<double>(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t s) {
-  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)s, 0));
+template <> __device__ __forceinline__ double buf1<double>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
 }
 
 // N consecutive elements in as few loads as they take.
 template <typename T, int N>
-__device__ __forceinline__ void buf_run(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t s, T (&v)[N]) {
+__device__ __forceinline__ void buf_run(__amdgpu_buffer_rsrc_t r, uint32_t off, T (&v)[N]) {
   constexpr int E = 16 / sizeof(T);
   typedef T vec_t __attribute__((ext_vector_type(E)));
   int f = 0;
 #pragma unroll
   for (; f + E <= N; f += E) {
     const vec_t q = __builtin_bit_cast(
-        vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off + f * (int)sizeof(T)), (int)s, 0));
+        vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off + f * (int)sizeof(T)), 0, 0));
 #pragma unroll
     for (int e = 0; e < E; ++e) v[f + e] = q[e];
   }
   if constexpr (sizeof(T) == 4) {
     if constexpr (N % 4 >= 2) {
       typedef float f2 __attribute__((ext_vector_type(2)));
-      const f2 q = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)(off + f * 4), (int)s, 0));
+      const f2 q = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)(off + f * 4), 0, 0));
       v[f] = q[0]; v[f + 1] = q[1];
       f += 2;
     }
   }
-  if constexpr (N % 2 == 1) v[f] = buf1<T>(r, off + f * (int)sizeof(T), s);
+  if constexpr (N % 2 == 1) v[f] = buf1<T>(r, off + f * (int)sizeof(T));
 }
 
 // Rows [i0, i0 + 16) of X into LDS, zero past row n and column p. Inside a group of 16 columns
@@ -180,8 +177,8 @@ __global__ __launch_bounds__((64 * sample_waves<T, F>())) void predict_samples(P
       auto load = [&](int s0, T (&b)[G][F]) {
 #pragma unroll
         for (int s = 0; s < G; ++s)
-          buf_run<T, F>(br, 4 * (s0 + s) + g < p ? voff : 0x40000000u,
-                        (uint32_t)((int64_t)4 * (s0 + s) * K * sizeof(T)), b[s]);
+          buf_run<T, F>(br, 4 * (s0 + s) + g < p ? voff + (uint32_t)(4 * (s0 + s) * K * (int)sizeof(T))
+                                                 : 0x40000000u, b[s]);
       };
       acc_t acc[F];
 #pragma unroll
@@ -275,7 +272,7 @@ __global__ __launch_bounds__(256) void predict_classes(PredictArgs a) {
             for (int q = 0; q < NB; ++q) {
               const int j = 4 * (s0 + s) + g, k = 16 * q + c;
               b[s][u][q] = buf1<T>(br, (j < p && k < kmax) ? (uint32_t)((u * pk + (int64_t)j * K + k) * sizeof(T))
-                                                           : 0x40000000u, 0);
+                                                           : 0x40000000u);
             }
       };
       acc_t acc[2][NB];
