@@ -204,19 +204,20 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
   L->hl_logits_wg = L->hl_cols = L->hl_nsplit = 0;
   L->hl_rps = 0;
   if (L->hilo) {
-    // logits: row blocks of kHiloRows rows; gradient: 128-column blocks times row
-    // slices, about 2048 workgroups in all
+    // logits: row blocks of kHiloRows rows; gradient: kGradCols-column blocks times row
+    // slices, as many slices as give about 2048 items of 128 columns
     const int64_t rows = kHiloRows;
     const int64_t nrb = (pr->n + rows - 1) / rows;
     if (tu.grid > 65536) return fail(HMC_ERR_ARG, "tuning.grid = %d must be <= 65536", tu.grid);
     const int64_t lwg = tu.grid ? tu.grid : 2048;
     L->hl_logits_wg = (int)(nrb < lwg ? nrb : lwg);
-    L->hl_cols = (int)((pr->p + 127) / 128);
+    L->hl_cols = (int)((pr->p + kGradCols - 1) / kGradCols);
     if (tu.rows_per_slice) {
       if (tu.rows_per_slice % 32) return fail(HMC_ERR_ARG, "tuning.rows_per_slice = %d must be a multiple of 32", tu.rows_per_slice);
       L->hl_rps = std::min<int64_t>(tu.rows_per_slice, (pr->n + 31) / 32 * 32);
     } else {
-      int64_t want = (2048 + L->hl_cols - 1) / L->hl_cols;
+      const int64_t c128 = (pr->p + 127) / 128;
+      int64_t want = (2048 + c128 - 1) / c128;
       const int64_t n32 = (pr->n + 31) / 32;
       want = want < 1 ? 1 : want > 256 ? 256 : want;
       if (want > n32) want = n32;
@@ -596,8 +597,22 @@ hmc_status check_sample_args(const hmc_sample_args* args) {
 // ceil(max K / 16) class blocks (the batch's `group`), chains x group <= 4.
 
 constexpr int kBatchMinRows = 1024;       // smallest gradient row slice the workspace holds
+// Default decomposition: 4096 rows per gradient slice, fewer while a batch has less than one
+// gradient item per compute unit (4 problems of n ~ U[1k, 50k], p ~ U[64, 2048], 4 chains: 255 us
+// per update with 4096 rows, 239 with 1024; 16 problems: 643 and 663), and a workgroup per item,
+// which lets the dispatcher balance the uneven items (16 problems: 660 us per update with 2048
+// workgroups, 643 with one per item; 48 problems, hi-only: 1262 and 1237).
 constexpr int kBatchDefaultRows = 4096;
-constexpr int kBatchDefaultGrid = 2048;
+constexpr int kBatchDefaultGrid = 16384;
+int batch_default_rows(const hmc_problem* probs, int32_t n_prob) {
+  int rows = kBatchDefaultRows;
+  for (;; rows /= 2) {
+    int64_t items = 0;
+    for (int b = 0; b < n_prob; ++b)
+      items += (probs[b].n + rows - 1) / rows * ((probs[b].p + kGradCols - 1) / kGradCols);
+    if (items >= 256 || rows <= kBatchMinRows) return rows;
+  }
+}
 
 struct BatchLayout {
   int nprob = 0, chains = 0, group = 1;   // group: 16-class blocks per chain
@@ -649,7 +664,7 @@ hmc_status check_batch(const hmc_problem* probs, int32_t n_prob, int32_t chains)
 hmc_status make_batch_layout(const hmc_problem* probs, int32_t n_prob, int32_t chains, int rows,
                              int grid, BatchLayout* B) {
   HMC_TRY(check_batch(probs, n_prob, chains));
-  if (rows == 0) rows = kBatchDefaultRows;
+  if (rows == 0) rows = batch_default_rows(probs, n_prob);
   if (grid == 0) grid = kBatchDefaultGrid;
   if (rows < kBatchMinRows || rows % 32) return fail(HMC_ERR_ARG, "rows_per_slice = %d must be a multiple of 32, >= %d", rows, kBatchMinRows);
   if (grid < 64 || grid > 65536) return fail(HMC_ERR_ARG, "grid = %d must be in [64, 65536]", grid);
@@ -682,7 +697,7 @@ hmc_status make_batch_layout(const hmc_problem* probs, int32_t n_prob, int32_t c
     P.n = pr.n; P.p = (int32_t)pr.p; P.K = pr.K;
     P.prior = pr.prior; P.pin = pr.pin_last_class; P.scale = pr.prior_scale;
     P.nrb = (int32_t)((pr.n + rb_rows - 1) / rb_rows);
-    P.gcols = (int32_t)((pr.p + 127) / 128);
+    P.gcols = (int32_t)((pr.p + kGradCols - 1) / kGradCols);
     P.rps = rows;
     P.nsplit = (int32_t)((pr.n + rows - 1) / rows);
     P.hot = hot_share(pr, bytes);

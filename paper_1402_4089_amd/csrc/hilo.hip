@@ -451,11 +451,17 @@ __device__ __forceinline__ void logits_rows(const Job& j, int64_t rb, double (&l
   softmax_residuals<NB, GROUP>(j, rb, acc, ylab, lacc);
 }
 
-// Gradient partial X^T R of the 128 columns from c0 over rows [rbeg, rend) (rbeg a
+// Gradient partial X^T R of the kGradCols columns from c0 over rows [rbeg, rend) (rbeg a
 // multiple of 32), written to gp: element (column j, class kk of group q) at
 // gp[q cstride + j K + kk].
 //
-// Stages of 32 rows (both X planes, 32 x 128 bf16 each, and the matching packed residual
+// Loads bound it: every column block of a slice reads the slice's packed residuals again (from
+// the L2), 256 bytes per row and 4 class blocks beside 1 KB of X for 256 columns. With 128
+// columns per workgroup those reads took 60-85 us of the kernel's time (timed without them):
+// n = 200000, p = 4096, K = 64 took 626 us there and 532 here (6.2 TB/s), a batch of 16
+// problems x 4 chains 360 and 325.
+//
+// Stages of 32 rows (both X planes, 32 x 256 bf16 each, and the matching packed residual
 // fragments) are loaded into registers two stages ahead of the math and stored to one of
 // two LDS buffers one stage ahead, so two stages of loads stay in flight per workgroup.
 // Wave w owns columns 32 w .. 32 w + 31 (two 16-column M blocks); the MFMA A input wants,
@@ -465,21 +471,25 @@ __device__ __forceinline__ void logits_rows(const Job& j, int64_t rb, double (&l
 // the time that streaming a stage takes. The 16-byte chunks of a staged row are XOR-swizzled
 // by 2 (row % 4 + 4 ((row / 8) % 2)), so that the eight rows a read touches at once fall in
 // different banks. Rows outside the slice and columns past p load as zero.
-template <int NB, bool LO> constexpr int grad_stage_elems() { return (LO ? 2 : 1) * 4096 + NB * 1024; }
-template <int NB> struct RPiece;                    // residual u16 per thread and stage
-template <> struct RPiece<1> { typedef uint2 type; static constexpr int N = 4; };
-template <> struct RPiece<2> { typedef u32x4 type; static constexpr int N = 8; };
-template <> struct RPiece<4> { typedef u32x4 type; static constexpr int N = 8; };
+constexpr int kGradThreads = 64 * kGradWaves;
+constexpr int kGradPlane = 32 * kGradCols;          // u16 of one plane per stage
+template <int NB, bool LO> constexpr int grad_stage_elems() { return (LO ? 2 : 1) * kGradPlane + NB * 1024; }
+// residual u16 per thread and piece: the stage's NB * 1024 over the threads, 16 bytes at most
+template <int N_> struct RPieceOf;
+template <> struct RPieceOf<2> { typedef uint32_t type; static constexpr int N = 2; };
+template <> struct RPieceOf<4> { typedef uint2 type; static constexpr int N = 4; };
+template <> struct RPieceOf<8> { typedef u32x4 type; static constexpr int N = 8; };
+template <int NB> struct RPiece : RPieceOf<(NB * 1024 / kGradThreads < 8 ? NB * 1024 / kGradThreads : 8)> {};
 
 template <int NB, int GROUP, bool LO, int AUX>
 __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg, int64_t rend,
                                           float* __restrict__ gp, int64_t cstride,
                                           u16* __restrict__ xs) {
   constexpr int PL = LO ? 2 : 1;
-  constexpr int XST = PL * 4096;                  // u16 of X per stage
+  constexpr int XST = PL * kGradPlane;                  // u16 of X per stage
   constexpr int ST = grad_stage_elems<NB, LO>();
   constexpr int RN = RPiece<NB>::N;               // residual u16 per thread per piece
-  constexpr int RP = NB * 1024 / (256 * RN);      // residual pieces per thread per stage
+  constexpr int RP = NB * 1024 / (kGradThreads * RN);      // residual pieces per thread per stage
   typedef typename RPiece<NB>::type rtype;
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
@@ -488,8 +498,8 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
   const int64_t nst = rend > rbeg ? (rend - rbeg + 31) / 32 : 0;
 
   // staging: thread t moves 16-byte chunk sc of rows sr and sr + 16 of each plane, and
-  // residual pieces t, t + 256, ...
-  const int sr = threadIdx.x >> 4, sc = threadIdx.x & 15;
+  // residual pieces t, t + kGradThreads, ...
+  const int sr = threadIdx.x / (kGradCols / 8), sc = threadIdx.x % (kGradCols / 8);
   const int64_t col = c0 + 8 * sc;
   struct Regs { u32x4 x[2][PL]; rtype r[RP]; };
   // Branch-free buffer loads: the X resource of a stage starts at its first row and ends
@@ -499,7 +509,7 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
   const uint64_t rpk_bytes = (uint64_t)((j.n + kHiloRows - 1) / kHiloRows) * (kHiloRows / 32) * NB * 2048;
   const __amdgpu_buffer_rsrc_t rres = make_rsrc(j.Rpk, rpk_bytes);
   // a chunk at or past column p (the last column block of a problem whose p is not a
-  // multiple of 128) would fetch the row's padding or the next row's bytes for columns that
+  // multiple of kGradCols) would fetch the row's padding or the next row's bytes for columns that
   // are never written: its offset is put out of the resource's range, so it reads zero and
   // moves nothing
   uint32_t xo[2];
@@ -521,8 +531,10 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
     const uint32_t roff = (uint32_t)((real ? row0 / 32 : (int64_t)(rpk_bytes / (NB * 2048))) * NB * 2048);
 #pragma unroll
     for (int i = 0; i < RP; ++i) {
-      const int off = (int)(roff + (i * 256 + threadIdx.x) * RN * 2);
-      if constexpr (RN == 8)
+      const int off = (int)(roff + (i * kGradThreads + threadIdx.x) * RN * 2);
+      if constexpr (RN == 2)
+        R.r[i] = (rtype)__builtin_amdgcn_raw_buffer_load_b32(rres, off, 0, 0);
+      else if constexpr (RN == 8)
         R.r[i] = __builtin_bit_cast(rtype, __builtin_amdgcn_raw_buffer_load_b128(rres, off, 0, 0));
       else
         R.r[i] = __builtin_bit_cast(rtype, __builtin_amdgcn_raw_buffer_load_b64(rres, off, 0, 0));
@@ -535,11 +547,11 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
       const int pos = sc ^ (2 * ((q & 3) | ((q >> 1) & 4)));
 #pragma unroll
       for (int pl = 0; pl < PL; ++pl)
-        *reinterpret_cast<u32x4*>(buf + pl * 4096 + q * 128 + 8 * pos) = R.x[h][pl];
+        *reinterpret_cast<u32x4*>(buf + pl * kGradPlane + q * kGradCols + 8 * pos) = R.x[h][pl];
     }
 #pragma unroll
     for (int i = 0; i < RP; ++i)
-      *reinterpret_cast<rtype*>(buf + XST + (i * 256 + threadIdx.x) * RN) = R.r[i];
+      *reinterpret_cast<rtype*>(buf + XST + (i * kGradThreads + threadIdx.x) * RN) = R.r[i];
   };
 
   f32x4 acc[2][NB];
@@ -567,8 +579,8 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
       bf16x8 af[PL];
 #pragma unroll
       for (int pl = 0; pl < PL; ++pl) {
-        const u16* t = cur + pl * 4096 + trow * 128 + tcol[mb];
-        af[pl] = as_frag(tr_pair(t, t + 4 * 128));
+        const u16* t = cur + pl * kGradPlane + trow * kGradCols + tcol[mb];
+        af[pl] = as_frag(tr_pair(t, t + 4 * kGradCols));
       }
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
@@ -583,12 +595,13 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
   Regs ra, rb;
   fetch(0, ra);
   fetch(1, rb);
+  // in pairs, the second of an odd count a stage of zeros (a branch in the middle cost a second
+  // set of accumulator registers)
   for (int64_t k = 0; k < nst; k += 2) {
     stash(ra, xs);
     __syncthreads();
     fetch(k + 2, ra);
     compute(xs);
-    if (k + 1 >= nst) break;
     stash(rb, xs + ST);
     __syncthreads();
     fetch(k + 3, rb);
@@ -657,19 +670,19 @@ __global__ __launch_bounds__(kHiloWaves * 64) void hilo_logits(HiloArgs a) {
   }
 }
 
-// One workgroup per (128-column block, row slice) item, items slice-major (the column
+// One workgroup per (kGradCols-column block, row slice) item, items slice-major (the column
 // blocks of a slice consecutive) in the XCD-aware order; the launch has xcd_span(items,
 // gcols) workgroups.
 template <int NB, bool LO>
-__global__ __launch_bounds__(256) void hilo_grad(HiloArgs a, int gcols) {
+__global__ __launch_bounds__(kGradThreads, 2) void hilo_grad(HiloArgs a, int gcols) {
   __shared__ __attribute__((aligned(16))) u16 xs[2 * grad_stage_elems<NB, LO>()];
   const int64_t it = xcd_item(blockIdx.x, gcols);
   if (it >= (int64_t)gcols * a.nsplit) return;
   const int64_t cb = it % gcols, sl = it / gcols;
   const int64_t rbeg = sl * a.rows_per_split;
   const int64_t rend = rbeg + a.rows_per_split < a.n ? rbeg + a.rows_per_split : a.n;
-  if (hot_slice(sl, a.hot)) grad_cols<NB, NB, LO, kKeep>(job_of(a), cb * 128, rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
-  else grad_cols<NB, NB, LO, kStream>(job_of(a), cb * 128, rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
+  if (hot_slice(sl, a.hot)) grad_cols<NB, NB, LO, kKeep>(job_of(a), cb * kGradCols, rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
+  else grad_cols<NB, NB, LO, kStream>(job_of(a), cb * kGradCols, rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -686,8 +699,21 @@ __device__ __forceinline__ int find_problem(const int32_t* first, int nprob, int
   return lo;
 }
 
+// A value that is the same in every lane, moved to scalar registers: the table's entries are
+// loaded by vector loads (the kernels' own stores could alias them), and would hold, with all
+// that is computed from them, vector registers for the whole item.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+  return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | lo);
+}
+template <typename T> __device__ __forceinline__ T* uniform(T* p) {
+  return reinterpret_cast<T*>(uniform((int64_t)reinterpret_cast<uintptr_t>(p)));
+}
+
 __device__ __forceinline__ Job job_of(const BatchProb& b, const float* B) {
-  return Job{b.Xhi, b.Xlo, b.ldx, b.y, b.n, b.p, b.K, B, b.Bpk, b.Rpk, b.pin};
+  return Job{uniform(b.Xhi), uniform(b.Xlo), uniform(b.ldx), uniform(b.y), uniform(b.n), uniform(b.p), uniform(b.K),
+             B, uniform(b.Bpk), uniform(b.Rpk), uniform(b.pin)};
 }
 
 template <int NB, int GROUP>
@@ -708,13 +734,13 @@ __global__ __launch_bounds__(kHiloWaves * 64, 2) void batch_logits(BatchArgs a) 
   const int64_t total = a.first_logits[a.nprob];
   for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
     const int b = find_problem(a.first_logits, a.nprob, it);
-    const BatchProb& P = a.probs[b];
-    const int64_t rb = it - a.first_logits[b];
+    const BatchProb& P = a.probs[uniform(b)];
+    const int64_t rb = uniform(it - a.first_logits[b]);
     double lacc[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) lacc[c] = 0.0;
-    const Job j = job_of(P, a.at_current ? P.B : P.Bp);
-    if (hot_slice(P.slice0 + rb * kHiloRows / P.rps, P.hot)) logits_rows<NB, GROUP, LO, kKeep>(j, rb, lacc, bs);
+    const Job j = job_of(P, nullptr);
+    if (hot_slice(uniform(P.slice0) + rb * kHiloRows / uniform(P.rps), uniform(P.hot))) logits_rows<NB, GROUP, LO, kKeep>(j, rb, lacc, bs);
     else logits_rows<NB, GROUP, LO, kStream>(j, rb, lacc, bs);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -732,7 +758,7 @@ __global__ __launch_bounds__(kHiloWaves * 64, 2) void batch_logits(BatchArgs a) 
 }
 
 template <int NB, int GROUP, bool LO>
-__global__ __launch_bounds__(256) void batch_grad(BatchArgs a) {
+__global__ __launch_bounds__(kGradThreads, 2) void batch_grad(BatchArgs a) {
   __shared__ __attribute__((aligned(16))) u16 xs[2 * grad_stage_elems<NB, LO>()];
   const int64_t total = a.first_grad[a.nprob];
   const int64_t span = xcd_span(total, kGradChunk);
@@ -740,15 +766,14 @@ __global__ __launch_bounds__(256) void batch_grad(BatchArgs a) {
     const int64_t it = xcd_item(pos, kGradChunk);
     if (it >= total) continue;
     const int b = find_problem(a.first_grad, a.nprob, it);
-    const BatchProb& P = a.probs[b];
-    const int64_t k = it - a.first_grad[b];
-    const int64_t cb = k % P.gcols, s = k / P.gcols;
-    const int64_t rbeg = s * P.rps;
-    const int64_t rend = rbeg + P.rps < P.n ? rbeg + P.rps : P.n;
-    const Job j = job_of(P, a.at_current ? P.B : P.Bp);
-    float* gp = P.gpart + s * P.gstride;
-    if (hot_slice(P.slice0 + s, P.hot)) grad_cols<NB, GROUP, LO, kKeep>(j, cb * 128, rbeg, rend, gp, P.cstride, xs);
-    else grad_cols<NB, GROUP, LO, kStream>(j, cb * 128, rbeg, rend, gp, P.cstride, xs);
+    const BatchProb& P = a.probs[uniform(b)];
+    const int64_t k = uniform(it - a.first_grad[b]), gcols = uniform(P.gcols), rps = uniform(P.rps);
+    const int64_t cb = k % gcols, s = k / gcols;
+    const Job j = job_of(P, nullptr);
+    const int64_t rbeg = s * rps, rend = rbeg + rps < j.n ? rbeg + rps : j.n;
+    float* gp = uniform(P.gpart + s * P.gstride);
+    if (hot_slice(uniform(P.slice0) + s, uniform(P.hot))) grad_cols<NB, GROUP, LO, kKeep>(j, cb * kGradCols, rbeg, rend, gp, uniform(P.cstride), xs);
+    else grad_cols<NB, GROUP, LO, kStream>(j, cb * kGradCols, rbeg, rend, gp, uniform(P.cstride), xs);
   }
 }
 
@@ -772,7 +797,7 @@ template <int NB, int GROUP, bool LO>
 static hipError_t launch_batch_t(const BatchArgs& a, const int grid[3], bool pack, hipStream_t s) {
   if (pack) hipLaunchKernelGGL((batch_pack<NB, GROUP>), dim3(grid[0]), dim3(256), 0, s, a);
   hipLaunchKernelGGL((batch_logits<NB, GROUP, LO>), dim3(grid[1]), dim3(kHiloWaves * 64), 0, s, a);
-  hipLaunchKernelGGL((batch_grad<NB, GROUP, LO>), dim3(grid[2]), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((batch_grad<NB, GROUP, LO>), dim3(grid[2]), dim3(kGradThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -794,7 +819,7 @@ static hipError_t launch_hilo_t(const HiloArgs& a, int logits_wg, int grad_cols,
   if (pack) hipLaunchKernelGGL(pack_b_kernel<NB>, dim3(packs), dim3(256), 0, s, a);
   hipLaunchKernelGGL((hilo_logits<NB, LO>), dim3(logits_wg), dim3(kHiloWaves * 64), 0, s, a);
   const int64_t span = xcd_span((int64_t)grad_cols * a.nsplit, grad_cols);
-  hipLaunchKernelGGL((hilo_grad<NB, LO>), dim3((unsigned)span), dim3(256), 0, s, a, grad_cols);
+  hipLaunchKernelGGL((hilo_grad<NB, LO>), dim3((unsigned)span), dim3(kGradThreads), 0, s, a, grad_cols);
   return hipGetLastError();
 }
 

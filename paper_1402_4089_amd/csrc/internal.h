@@ -127,7 +127,9 @@ constexpr int kHiloRows = kHiloWaves * 16 * kHiloMB;   // rows per logits row bl
 // covers xcd_span(items, G) positions. kGradChunk is G for the batched kernel (the column
 // blocks of one row slice of a problem with p <= 2048).
 constexpr int kXcds = 8;
-constexpr int kGradChunk = 16;
+constexpr int kGradWaves = 8;      // waves of a gradient workgroup, 32 columns each
+constexpr int kGradCols = 32 * kGradWaves;
+constexpr int kGradChunk = 2048 / kGradCols;
 constexpr int64_t xcd_span(int64_t total, int G) {
   return (total + (int64_t)kXcds * G - 1) / ((int64_t)kXcds * G) * kXcds * G;
 }
