@@ -233,16 +233,19 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
   } else if (L->wide) {
     const int cw = L->f64 ? wide_chunk_cols<double>() : wide_chunk_cols<float>();
     L->nchunk = (int)((pr->p + cw - 1) / cw);
-    // enough logits workgroups to fill the chip, at least 16 tile rows per chunk
-    int64_t ty = (1024 + L->nchunk - 1) / L->nchunk;
-    ty = ty < 16 ? 16 : ty;
+    // as many logits workgroups as run at once: more leave a partly filled last round, and a
+    // count between multiples of the 256 compute units loads them unevenly (n = 2000,
+    // p = 50000, K = 4: 157 us per gradient with 15 workgroups per chunk, 162 with 21; n = 10000,
+    // p = 20000, K = 20: 374 with 25, 413 with 52; n = 3000, p = 1200, K = 40: 41 with 128, 47
+    // with all 188 tiles)
+    const int64_t ty = std::max<int64_t>(1, 256 * wide_logits_resident(L->nb) / L->nchunk);
+    L->tiles_y = (int)(L->ntiles < ty ? L->ntiles : ty);
     if (tu.grid) {
       if (tu.grid > 65535) return fail(HMC_ERR_ARG, "tuning.grid = %d must be <= 65535 on the wide-p path", tu.grid);
-      ty = tu.grid;
+      L->tiles_y = (int)(L->ntiles < tu.grid ? L->ntiles : tu.grid);
     }
-    L->tiles_y = (int)(L->ntiles < ty ? L->ntiles : ty);
-    L->nsoft = (int)((pr->n + 3) / 4);               // softmax workgroups of 4 rows
-    L->ngrad = wide_grad_groups(pr->p, L->nb, L->f64);
+    L->nsoft = (int)(4 * L->ntiles);                 // softmax workgroups of 4 rows, whole tiles
+    L->ngrad = wide_grad_groups(pr->p, L->f64);
     // few column blocks: split the rows too (partials reduced by the shared epilogue)
     L->wsplit = 1;
     L->wtps = 0;
@@ -253,9 +256,9 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
         L->wtps = tps;
         L->wsplit = (int)((L->ntiles + tps - 1) / tps);
       }
-    } else if (L->ngrad < 512) {
+    } else {
       const int64_t groups = (L->ntiles + 3) / 4;                  // 4-tile groups (load pairs)
-      int64_t want = (512 + L->ngrad - 1) / L->ngrad;
+      int64_t want = wide_row_slices(pr->p, L->nb, L->f64);
       want = want > groups ? groups : want;
       if (want > 1) {
         L->wtps = (groups + want - 1) / want * 4;
@@ -284,7 +287,7 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
   size_t off = 0;
   L->off_gpart = off; off = align_up(off + (size_t)L->nwg * L->gstride * L->ts);
   L->off_zpart = off; off = align_up(off + (L->wide ? (size_t)L->nchunk * pr->n * KP * L->ts : 0));
-  L->off_R = off;     off = align_up(off + (L->wide ? (size_t)pr->n * KP * L->ts : 0));
+  L->off_R = off;     off = align_up(off + (L->wide ? (size_t)L->ntiles * kTileRows * KP * L->ts : 0));
   {
     const size_t frag = 2 * 512 * sizeof(uint16_t);   // one hi/lo pair of 64-lane fragments
     const int64_t rows = kHiloRows;

@@ -101,7 +101,7 @@ struct WideArgs {
   int32_t p, K;
   int32_t nchunk;       // column chunks of wide_logits
   void* zpart;          // [nchunk][n][16*NB] partial logits
-  void* R;              // [n][16*NB] residuals
+  void* R;              // residuals [16-row tile][NB][64 lanes][4 steps] (gradient operand order)
   double* lpart;        // [ceil(n/16)] log-likelihood partials
   double* ppart;        // [gradient workgroups] prior log-density partials
   double* kpart;        // [gradient workgroups] kinetic partials (mode 2)
@@ -232,7 +232,9 @@ template <typename T> hipError_t launch_accept(const AcceptArgs& a, int nwg, hip
 hipError_t launch_final(const FinalArgs& a, hipStream_t s);
 
 template <typename T> int wide_chunk_cols();
-int wide_grad_groups(int64_t p, int nb, bool f64);
+int wide_grad_groups(int64_t p, bool f64);
+int wide_row_slices(int64_t p, int nb, bool f64);
+int wide_logits_resident(int nb);
 template <typename T>
 hipError_t launch_wide(const WideArgs& a, int nb, int logits_tiles_y, int softmax_wg, int grad_wg,
                        hipStream_t s);

@@ -5,13 +5,13 @@
 // kernels because a row's logits need all p columns before its residuals exist:
 //   wide_logits   16-row x 1024-column blocks of X on MFMA -> per-chunk partial logits
 //   wide_softmax  sums the chunk partials of a row, softmax, residuals R, log-likelihood
-//   wide_grad     each workgroup owns an even share of the 16-column blocks, streams the
-//                 rows of X and R (all of them, or one row slice) through MFMA
-//                 (G block = X^T R); with all rows it then applies prior, mask and the
-//                 leapfrog kicks and drift to its own columns (no cross-workgroup
-//                 reduction), with row slices it writes partials for the shared epilogue.
-// X is read twice per gradient. All loads go through buffer resources whose bounds
-// make rows past n read as zero.
+//   wide_grad     each wave owns 256 bytes of columns, streams the rows of X and R (all of
+//                 them, or one row slice) through MFMA (G block = X^T R); with all rows it
+//                 then applies prior, mask and the leapfrog kicks and drift to its own
+//                 columns (no cross-workgroup reduction), with row slices it writes partials
+//                 for the shared epilogue.
+// X is read twice per gradient, which bounds the path: the matrix cores are busy a third of the
+// time. All loads go through buffer resources whose bounds make rows past n read as zero.
 #include "device_common.h"
 
 namespace hmcx {
@@ -22,15 +22,13 @@ namespace {
 
 constexpr int kWideWaves = 4;
 
-__device__ __forceinline__ float4 ld16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
-}
-template <typename T> __device__ __forceinline__ T ld1(__amdgpu_buffer_rsrc_t r, uint32_t off);
-template <> __device__ __forceinline__ float ld1<float>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-}
-template <> __device__ __forceinline__ double ld1<double>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+// Columns of a logits workgroup.
+template <typename T> constexpr int wide_chunk() { return kWideWaves * (sizeof(T) == 4 ? 16 : 8) * 16; }
+
+// 16 bytes of X or R: 4 floats or 2 doubles.
+template <typename T> using vec16 = T __attribute__((ext_vector_type(16 / sizeof(T))));
+template <typename T> __device__ __forceinline__ vec16<T> ld16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(vec16<T>, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }
 
 // Partial logits over one column chunk for the row tiles tile0, tile0 + tstep, ...
@@ -42,7 +40,7 @@ __global__ __launch_bounds__(kWideWaves * 64) void wide_logits(WideArgs a) {
   using M = Mma<T>;
   using acc_t = typename M::acc;
   constexpr int MBW = sizeof(T) == 4 ? 16 : 8;
-  constexpr int CW = kWideWaves * MBW * 16;
+  constexpr int CW = wide_chunk<T>();
   __shared__ __align__(16) T zb[kWideWaves * NB * 256];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -87,12 +85,11 @@ __global__ __launch_bounds__(kWideWaves * 64) void wide_logits(WideArgs a) {
       const bool live = col0 < p;
       const uint32_t off = live ? (uint32_t)(((int64_t)c * ldx + col0) * sizeof(T)) : 0xFFFFFFE0u;
       if constexpr (sizeof(T) == 4) {
-        const float4 q = ld16(xr, off);
-        av[m][0] = q.x; av[m][1] = q.y; av[m][2] = q.z; av[m][3] = q.w;
+        const vec16<T> q = ld16<T>(xr, off);
+        av[m][0] = q[0]; av[m][1] = q[1]; av[m][2] = q[2]; av[m][3] = q[3];
       } else {
-        const double2 q0 = __builtin_bit_cast(double2, ld16(xr, off));
-        const double2 q1 = __builtin_bit_cast(double2, ld16(xr, off + 16));
-        av[m][0] = q0.x; av[m][1] = q0.y; av[m][2] = q1.x; av[m][3] = q1.y;
+        const vec16<T> q0 = ld16<T>(xr, off), q1 = ld16<T>(xr, off + 16);
+        av[m][0] = q0[0]; av[m][1] = q0[1]; av[m][2] = q1[0]; av[m][3] = q1[1];
       }
       if (maskcols) {
 #pragma unroll
@@ -163,14 +160,17 @@ __global__ __launch_bounds__(256) void wide_softmax(WideArgs a) {
     zz[nb] = ((zs[0][nb][lane] + zs[1][nb][lane]) + zs[2][nb][lane]) + zs[3][nb][lane];
   const int yi = a.y[ic];
   double l = 0.0;
-  T* R = static_cast<T*>(a.R);
+  // residuals in the lane order of the gradient's B operand: [16-row tile][block][lane][step],
+  // row M::row(s, g) of the tile at step s of lane 16 g + c; rows past n are zero
+  const int rt = (int)(i & 15), rs = sizeof(T) == 4 ? rt & 3 : rt >> 2, rg = sizeof(T) == 4 ? rt >> 2 : rt & 3;
+  T* R = static_cast<T*>(a.R) + ((i >> 4) * NB * 64 + 16 * rg + c) * 4 + rs;
   if (a.link == 1) {
     // Poisson link, one coefficient column (lane c = 0): residual y - exp(z), term y z - exp(z)
     const T mu = dev_exp(zz[0]);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const int k = nb * 16 + c;
-      if (valid) R[i * KP + k] = k == 0 ? T(yi) - mu : T(0);
+      R[nb * 256] = valid && k == 0 ? T(yi) - mu : T(0);
     }
     l = (valid && c == 0) ? (double)yi * (double)zz[0] - (double)mu : 0.0;
   } else if (a.link == 2) {
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) void wide_softmax(WideArgs a) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const int k = nb * 16 + c;
-      if (valid) R[i * KP + k] = k == 0 ? sg * ratio : T(0);
+      R[nb * 256] = valid && k == 0 ? sg * ratio : T(0);
     }
     l = (valid && c == 0) ? lp : 0.0;
   } else {
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(256) void wide_softmax(WideArgs a) {
     for (int nb = 0; nb < NB; ++nb) {
       const int k = nb * 16 + c;
       const bool hit = valid && k == yi;
-      if (valid) R[i * KP + k] = (k < K) ? ((hit ? T(1) : T(0)) - ex[nb] * inv) : T(0);
+      R[nb * 256] = valid && k < K ? ((hit ? T(1) : T(0)) - ex[nb] * inv) : T(0);
       l += hit ? (double)((zz[nb] - mx) - lse_shift) : 0.0;
     }
   }
@@ -213,50 +213,36 @@ __global__ __launch_bounds__(256) void wide_softmax(WideArgs a) {
   if (lane == 0) a.lpart[blockIdx.x] = l;
 }
 
-// Blocks of 16 gradient columns a wave of the column-owner kernel can hold (accumulators and
-// two load groups in registers): fewer for more class blocks and for float64.
-template <typename T, int NB> constexpr int wide_wave_blocks() {
-  return (sizeof(T) == 4 ? 4 : 2) / NB > 0 ? (sizeof(T) == 4 ? 4 : 2) / NB : 1;
-}
-
-// Column-owner gradient. The ceil(p/16) column blocks are shared out evenly: workgroup x owns
-// blocks [x nblk / gridDim.x, (x + 1) nblk / gridDim.x) (at most 4 CB of them), and wave w
-// takes the workgroup's blocks w, w + 4, ... (CB at most). An even share keeps every compute
-// unit streaming the same number of columns, where whole 128-column workgroups left some units
-// with two and others with one. With one row slice (gridDim.y == 1) the workgroup applies the
-// leapfrog epilogue to its own columns; with several, slice blockIdx.y covers tiles_per_split
-// 16-row tiles (a multiple of the U-tile load group) and writes its partial X^T R to gpart for
-// the shared epilogue kernel.
+// Column-owner gradient. A wave owns 256 bytes of a row, 16 E consecutive columns. A lane's 16-byte load
+// takes E consecutive columns of one row; as which column of G a row of the MFMA's output means
+// is free, element e of the load is the A operand of a block that holds columns E c + e, c = 0
+// .. 15: one instruction reads 4 rows x 256 bytes and feeds E blocks (loads of one element per
+// lane had taken E times the instructions, of 64 bytes per row). With one row slice (gridDim.y
+// == 1) the workgroup applies the leapfrog epilogue to its own columns; with several, slice
+// blockIdx.y covers tiles_per_split 16-row tiles (a multiple of the U-tile load group) and writes
+// its partial X^T R to gpart for the shared epilogue kernel. Measured against one element per
+// lane: n = 2000, p = 50000, K = 4, FP32 75.5 -> 71.4 us (5.6 TB/s); a whole gradient of
+// n = 5000, p = 1000, K = 10, FP64 46 -> 33 us, n = 2000, p = 10000, K = 4, FP64 84 -> 64 us.
 template <typename T, int NB>
-__global__ __launch_bounds__(kWideWaves * 64) void wide_grad(WideArgs a) {
+__global__ __launch_bounds__(kWideWaves * 64, (sizeof(T) * NB <= 8 ? 3 : sizeof(T) * NB <= 16 ? 2 : 1)) void wide_grad(WideArgs a) {
+  __shared__ double sh4[2][4];
   using M = Mma<T>;
   using acc_t = typename M::acc;
-  constexpr int KP = 16 * NB, CB = wide_wave_blocks<T, NB>(), U = 2;   // U row tiles per load group
-  __shared__ double sh4[2][4];
+  constexpr int E = 16 / sizeof(T), U = 2;               // U row tiles per load group
+  constexpr int RB = 4 / E;                              // 16-byte loads of a tile's residual operand
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, c = lane & 15;
   const int p = a.p, K = a.K;
   const int64_t n = a.n, ldx = a.ldx;
-  const int64_t nblk = (p + 15) / 16;
-  const int64_t b0 = (int64_t)blockIdx.x * nblk / gridDim.x;
-  const int64_t b1 = (int64_t)(blockIdx.x + 1) * nblk / gridDim.x;
-  // first column of this wave's block cb, and whether that block belongs to the workgroup
-  int jb[CB];
-  bool live[CB];
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    const int64_t b = b0 + w + kWideWaves * cb;
-    live[cb] = b < b1;
-    jb[cb] = (int)((live[cb] ? b : b0) * 16);
-  }
+  const int j0 = ((int)blockIdx.x * kWideWaves + w) * 16 * E;   // first column of this wave
 
   const uint64_t x_bytes = (uint64_t)((n - 1) * ldx + p) * sizeof(T);
-  acc_t gacc[CB][NB];
+  acc_t gacc[E][NB];
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
+  for (int e = 0; e < E; ++e)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) gacc[cb][nb] = acc_t{0, 0, 0, 0};
+    for (int nb = 0; nb < NB; ++nb) gacc[e][nb] = acc_t{0, 0, 0, 0};
   const int64_t ntiles = (n + kTileRows - 1) / kTileRows;
   const int64_t tbeg = (int64_t)blockIdx.y * a.tiles_per_split;
   const int64_t tend = gridDim.y == 1 ? ntiles : (tbeg + a.tiles_per_split < ntiles ? tbeg + a.tiles_per_split : ntiles);
@@ -266,29 +252,35 @@ __global__ __launch_bounds__(kWideWaves * 64) void wide_grad(WideArgs a) {
   // last rows of X, so the first groups here may still be held by the memory-side cache.
   // Group k - 1 is loaded while group k is multiplied; a group index below 0 gets
   // resources without records, so its loads return zeros without touching memory and
-  // the issue stays free of branches. A block outside the workgroup's share loads from an
-  // offset past every resource's end: zeros, no traffic.
-  struct Regs { T xa[U][CB][4], ra[U][NB][4]; };
+  // the issue stays free of branches. A lane whose columns lie past p loads from an
+  // offset past every resource's end: zeros, no traffic (columns past p only feed columns of
+  // G that are not written).
+  struct Regs { vec16<T> xa[U][4], ra[U][NB][RB]; };
+  const bool live = j0 + c * E < p;
+  uint32_t xoff[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) xoff[s] = (uint32_t)(((int64_t)M::row(s, g) * ldx + j0 + c * E) * sizeof(T));
+  const uint32_t xstep = (uint32_t)(kTileRows * ldx * sizeof(T));
   auto load = [&](int64_t k, Regs& rg) {
     const bool real = k >= 0;
     const int64_t t0 = tbeg + (real ? k : 0) * U;
     const uint64_t base = (uint64_t)(t0 * kTileRows) * ldx * sizeof(T);
+    const uint64_t rbase = (uint64_t)t0 * NB * 256 * sizeof(T), rall = (uint64_t)ntiles * NB * 256 * sizeof(T);
     const __amdgpu_buffer_rsrc_t xr =
         make_rsrc(static_cast<const char*>(a.X) + base, real ? x_bytes - base : 0);
-    const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.R, real ? (uint64_t)n * KP * sizeof(T) : 0);
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(static_cast<const char*>(a.R) + rbase, real ? rall - rbase : 0);
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u) {
+      // the second tile of a slice's odd count belongs to the next slice: not read
+      const bool in = t0 + u < tend;
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int row = u * kTileRows + M::row(s, g);           // relative to t0's first row
+      for (int s = 0; s < 4; ++s) rg.xa[u][s] = ld16<T>(xr, in && live ? xoff[s] + u * xstep : 0xFFFFFFF0u);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-          rg.xa[u][cb][s] = ld1<T>(xr, live[cb] ? (uint32_t)(((int64_t)row * ldx + jb[cb] + c) * sizeof(T))
-                                                : 0xFFFFFFF0u);
+      for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          rg.ra[u][nb][s] = ld1<T>(rr, (uint32_t)(((t0 * kTileRows + row) * KP + nb * 16 + c) * sizeof(T)));
-      }
+        for (int q = 0; q < RB; ++q)
+          rg.ra[u][nb][q] = ld16<T>(rr, in ? (uint32_t)((((u * NB + nb) * 64 + lane) * RB + q) * 16) : 0xFFFFFFF0u);
+    }
   };
   auto mma = [&](const Regs& rg) {
 #pragma unroll
@@ -296,14 +288,14 @@ __global__ __launch_bounds__(kWideWaves * 64) void wide_grad(WideArgs a) {
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
+        for (int e = 0; e < E; ++e)
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb)
-            gacc[cb][nb] = M::run(rg.xa[u][cb][s], rg.ra[u][nb][s], gacc[cb][nb]);
+            gacc[e][nb] = M::run(rg.xa[u][s][e], rg.ra[u][nb][s / E][s % E], gacc[e][nb]);
   };
   // Explicit waits leave the group just issued in flight (the compiler, left to itself,
   // waits for every load before the first MFMA of the rotated loop).
-  constexpr int GL = U * 4 * (CB + NB);                 // loads per group
+  constexpr int GL = U * (4 + NB * RB);            // loads per group
   static_assert(GL < 64, "vmcnt range");
   // Groups are taken in pairs; with an odd count the last pair's second group is one of
   // zeros, whose products add nothing.
@@ -318,16 +310,18 @@ __global__ __launch_bounds__(kWideWaves * 64) void wide_grad(WideArgs a) {
     mma(r1);
   }
 
+  // row r of accumulator e is column j0 + E row + e
+  auto column = [&](int e, int r) { return j0 + M::row(r, g) * E + e; };
   if (gridDim.y > 1) {
     T* gp = static_cast<T*>(a.gpart) + (int64_t)blockIdx.y * a.gstride;
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int j = jb[cb] + M::row(r, g), k = nb * 16 + c;
-          if (live[cb] && j < p && k < K) gp[(int64_t)j * K + k] = gacc[cb][nb][r];
+        for (int e = 0; e < E; ++e) {
+          const int j = column(e, r), k = nb * 16 + c;
+          if (j < p && k < K) gp[(int64_t)j * K + k] = gacc[e][nb][r];
         }
     return;
   }
@@ -339,18 +333,18 @@ __global__ __launch_bounds__(kWideWaves * 64) void wide_grad(WideArgs a) {
   T* Gv = static_cast<T*>(a.G);
   double pr = 0.0, ke = 0.0;
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int j = jb[cb] + M::row(r, g), k = nb * 16 + c;
-        if (!live[cb] || j >= p || k >= K) continue;
+      for (int el = 0; el < E; ++el) {
+        const int j = column(el, r), k = nb * 16 + c;
+        if (j >= p || k >= K) continue;
         const int64_t e = (int64_t)j * K + k;
         const bool pinned = a.pin && k == K - 1;
         const T bt = Bv[e];
         const double b = (double)bt;
-        const T gt = pinned ? T(0) : (T)((double)gacc[cb][nb][r] + prior_grad(b, a.prior, a.scale));
+        const T gt = pinned ? T(0) : (T)((double)gacc[el][nb][r] + prior_grad(b, a.prior, a.scale));
         Gv[e] = gt;
         pr += pinned ? 0.0 : prior_logd(b, a.prior, a.scale);
         if (a.mode != 0) {
@@ -378,24 +372,27 @@ __global__ __launch_bounds__(kWideWaves * 64) void wide_grad(WideArgs a) {
 }  // namespace
 
 template <typename T>
-int wide_chunk_cols() { return kWideWaves * (sizeof(T) == 4 ? 16 : 8) * 16; }
-// Workgroups of the column-owner gradient for p columns and NB class blocks: enough that none
-// holds more than 4 CB blocks of 16 columns, in whole rounds of 256 compute units from 256 on.
-// Below that, 256 workgroups while that still gives every wave two blocks or more (at n = 2000,
-// p = 50000, 256 workgroups of 12-13 blocks on two row slices streamed faster than 512 of 6 on
-// one), and otherwise the fewest workgroups whose waves hold CB blocks each, the rows being
-// split over more slices instead: a wave with one or two blocks keeps too few loads in flight
-// (plan replays, FP32: n = 20000, K = 10 at p = 12000 / 16400 / 24000 took 458 / 618 / 910 us
-// per gradient against 611 / 771 / 953 us with one block per wave in 256 workgroups, and the
-// 36 problems of the batched workload with p > 1024 took 24% less time in all).
-int wide_grad_groups(int64_t p, int nb, bool f64) {
+int wide_chunk_cols() { return wide_chunk<T>(); }
+// Workgroups of the column-owner gradient for p columns.
+int wide_grad_groups(int64_t p, bool f64) {
+  const int64_t cols = (int64_t)kWideWaves * (f64 ? 32 : 64);
+  return (int)((p + cols - 1) / cols);
+}
+// Row slices wanted for p columns: about 512 / g with g the workgroups that hold at most 4 (2 in
+// float64, fewer with more class blocks) blocks of 16 columns per wave, in whole rounds of 256
+// from 256 on and 256 while that leaves a wave two blocks. More slices made some shapes 4-8%
+// faster and others as much slower.
+int wide_row_slices(int64_t p, int nb, bool f64) {
   const int64_t nblk = (p + 15) / 16;
   const int cb = f64 ? (nb == 1 ? 2 : 1) : (nb == 1 ? 4 : nb == 2 ? 2 : 1);
-  const int64_t need = (nblk + kWideWaves * cb - 1) / (kWideWaves * cb);
-  if (need >= 256) return (int)((need + 255) / 256 * 256);
-  if (nblk >= (int64_t)kWideWaves * 256 * 2) return 256;
-  return (int)need;
+  int64_t g = (nblk + kWideWaves * cb - 1) / (kWideWaves * cb);
+  if (g >= 256) g = (g + 255) / 256 * 256;
+  else if (nblk >= (int64_t)kWideWaves * 256 * 2) g = 256;
+  return g < 512 ? (int)((512 + g - 1) / g) : 1;
 }
+// Logits workgroups a compute unit holds at once (registers: 163, 235 and 375 per lane with 1, 2
+// and 4 class blocks).
+int wide_logits_resident(int nb) { return nb == 1 ? 3 : nb == 2 ? 2 : 1; }
 
 template <typename T>
 hipError_t launch_wide(const WideArgs& a, int nb, int logits_tiles_y, int softmax_wg, int grad_wg,
