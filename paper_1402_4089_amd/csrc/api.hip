@@ -25,7 +25,7 @@ struct Profiler {
   int cap = 0, used = 0;
   int repeat = 1;             // launches per event pair when the pass is idempotent
   hipEvent_t* ev = nullptr;   // 2 * cap events
-  int* reps = nullptr;        // launches between each recorded pair
+  int* reps = nullptr;        // gradient passes between each recorded pair
 } g_prof;
 
 hmc_status fail(hmc_status s, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
@@ -52,6 +52,7 @@ struct Layout {
   int nwg, nepi, nupd;
   int64_t gstride;      // elements between per-workgroup partial gradients
   bool wide;            // p beyond the row tile: chunked logits + column-owner gradient
+  bool tiny;            // small problem: everything in one workgroup
   int nchunk, tiles_y, nsoft, ngrad, wsplit;
   int64_t wtps;         // wide gradient: 16-row tiles per row slice
   bool hilo, lo;        // bf16 split-precision form (lo: the low plane is present)
@@ -166,6 +167,7 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
   if (L->hilo != (tu.path == 3) && tu.path != 0)
     return fail(HMC_ERR_ARG, "tuning.path %d does not fit X format %d (path 3 is the bf16 formats' only path)",
                 tu.path, pr->xfmt);
+  L->tiny = !L->hilo && tu.path == 0 && tiny_fits(pr->n, pr->p, pr->K, L->f64);
   if (tu.path == 1 || tu.path == 0) {
     const bool ruled = tu.waves == 0 && tu.mb == 0;
     bool ok;
@@ -426,14 +428,15 @@ hmc_status hip_status(hipError_t e, const char* what) {
 // events on its stream; an idempotent pass (one that only overwrites workspace) runs
 // g_prof.repeat times back to back between the pair, which spreads the cost of recording
 // the events over several launches.
+// `passes` is the number of gradient passes in one launch.
 template <typename F>
-hmc_status timed_launch(hipStream_t s, bool idempotent, F&& launch) {
+hmc_status timed_launch(hipStream_t s, bool idempotent, F&& launch, int passes = 1) {
   if (!(g_prof.on && g_prof.used < g_prof.cap)) return launch();
   const int reps = idempotent ? g_prof.repeat : 1;
   HMC_TRY(hip_status(hipEventRecord(g_prof.ev[2 * g_prof.used], s), "profile event"));
   for (int r = 0; r < reps; ++r) HMC_TRY(launch());
   HMC_TRY(hip_status(hipEventRecord(g_prof.ev[2 * g_prof.used + 1], s), "profile event"));
-  g_prof.reps[g_prof.used] = reps;
+  g_prof.reps[g_prof.used] = reps * passes;
   ++g_prof.used;
   return HMC_OK;
 }
@@ -515,9 +518,23 @@ hmc_status gradient_step(const hmc_problem* pr, const Layout& L, const void* Bpo
   return hip_status(launch_epilogue<T>(e, L.nepi, s), "gradient epilogue");
 }
 
+// The common arguments of the one-workgroup form.
+TinyArgs tiny_args(const hmc_problem* pr, void* B, void* G, double* logpost, double eps, int L_steps, int mode) {
+  TinyArgs a{};
+  a.X = pr->X; a.ldx = pr->ldx; a.y = pr->y; a.n = pr->n; a.p = (int32_t)pr->p; a.K = pr->K;
+  a.link = pr->link; a.pin = pr->pin_last_class; a.prior = pr->prior; a.scale = pr->prior_scale;
+  a.mode = mode; a.L = L_steps; a.h = 0.5 * eps; a.eps = eps;
+  a.B = B; a.G = G; a.logpost = logpost;
+  return a;
+}
+
 template <typename T>
 hmc_status do_logpost_grad(const hmc_problem* pr, const Layout& L, const void* B, double* logpost,
                            void* G, void* ws, hipStream_t s) {
+  if (L.tiny) {
+    const TinyArgs a = tiny_args(pr, const_cast<void*>(B), G, logpost, 0.0, 1, 0);
+    return timed_launch(s, true, [&] { return hip_status(launch_tiny<T>(a, s), "one-workgroup gradient"); });
+  }
   HMC_TRY(gradient_step<T>(pr, L, B, G, nullptr, 0, 0.0, ws, s));
   FinalArgs fa{at<double>(ws, L.off_lpart), L.nl, at<double>(ws, L.off_ppart), L.np, logpost};
   return hip_status(launch_final(fa, s), "log-posterior final sum");
@@ -526,6 +543,11 @@ hmc_status do_logpost_grad(const hmc_problem* pr, const Layout& L, const void* B
 template <typename T>
 hmc_status do_leapfrog(const hmc_problem* pr, const Layout& L, void* B, void* eta, void* G,
                        double* logpost, double eps, int L_steps, void* ws, hipStream_t s) {
+  if (L.tiny) {
+    TinyArgs a = tiny_args(pr, B, G, logpost, eps, L_steps, 1);
+    a.eta = eta;
+    return timed_launch(s, false, [&] { return hip_status(launch_tiny<T>(a, s), "one-workgroup leapfrog"); }, L_steps);
+  }
   StartArgs sa{};
   sa.p = (int32_t)pr->p; sa.K = pr->K; sa.pin = pr->pin_last_class;
   sa.B = B; sa.G = G; sa.Bp = B; sa.eta = eta; sa.h = 0.5 * eps; sa.eps = eps; sa.draw = 0;
@@ -538,11 +560,20 @@ hmc_status do_leapfrog(const hmc_problem* pr, const Layout& L, void* B, void* et
 
 // One HMC iteration (momentum draw, L leapfrog updates, Metropolis test) enqueued on s.
 // Record slot t and iteration first_iter + t come from the arguments, or, when ctr is a
-// device counter {iteration, first iteration}, from device memory at run time (graphs).
+// device counter {iteration, first iteration}, from device memory at run time (graphs); the
+// counter is then advanced.
 template <typename T>
 hmc_status enqueue_iteration(const hmc_problem* pr, const Layout& L, void* B, void* G,
                              double* logpost, const hmc_sample_args* ar, void* ws, hipStream_t s,
-                             int64_t t, const int64_t* ctr) {
+                             int64_t t, int64_t* ctr) {
+  if (L.tiny) {
+    TinyArgs a = tiny_args(pr, B, G, logpost, ar->eps, ar->L, 2);
+    a.draw = ar->replay_normals ? 1 : 2; a.normals = ar->replay_normals; a.replay_u = ar->replay_uniforms;
+    a.inv_temp = ar->inv_temperature; a.seed = ar->seed; a.chain = ar->chain;
+    a.iter = (int64_t)ar->first_iter + t; a.t = t; a.n_rec = ar->n_iter; a.ctr = ctr;
+    a.sample = ar->samples; a.accepted = ar->accepted; a.H = ar->H; a.divergent = ar->divergent;
+    return timed_launch(s, false, [&] { return hip_status(launch_tiny<T>(a, s), "one-workgroup transition"); }, ar->L);
+  }
   void* eta = at<void>(ws, L.off_eta);
   void* Bp = at<void>(ws, L.off_bp);
   void* Gp = at<void>(ws, L.off_gp);
@@ -573,7 +604,8 @@ hmc_status enqueue_iteration(const hmc_problem* pr, const Layout& L, void* B, vo
   aa.accepted = ar->accepted;
   aa.H = ar->H;
   aa.divergent = ar->divergent;
-  return hip_status(launch_accept<T>(aa, L.nupd, s), "accept");
+  HMC_TRY(hip_status(launch_accept<T>(aa, L.nupd, s), "accept"));
+  return ctr ? hip_status(launch_counter(ctr, 0, 1, s), "iteration counter") : HMC_OK;
 }
 
 template <typename T>
@@ -1197,9 +1229,8 @@ hmc_status hmc_plan_create(hmc_plan** plan, const hmc_problem* prob, void* B, vo
   const hmc_sample_args ar = *args;
   const hmc_problem pr = *prob;
   hmc_status st = capture(P, [&](hipStream_t cs) -> hmc_status {
-    HMC_TRY(L.f64 ? enqueue_iteration<double>(&pr, L, B, G, logpost, &ar, ws, cs, 0, P->ctr)
-                  : enqueue_iteration<float>(&pr, L, B, G, logpost, &ar, ws, cs, 0, P->ctr));
-    return hip_status(launch_counter(P->ctr, 0, 1, cs), "iteration counter");
+    return L.f64 ? enqueue_iteration<double>(&pr, L, B, G, logpost, &ar, ws, cs, 0, P->ctr)
+                 : enqueue_iteration<float>(&pr, L, B, G, logpost, &ar, ws, cs, 0, P->ctr);
   });
   if (st != HMC_OK) {
     hmc_plan_destroy(P);

@@ -216,6 +216,28 @@ struct PredictArgs {
   int32_t* classes;     // [n] or null
 };
 
+// A gradient, L leapfrog updates or a transition of a small problem in one workgroup.
+struct TinyArgs {
+  const void* X; int64_t ldx;
+  const int32_t* y;
+  int64_t n;
+  int32_t p, K, link, pin, prior;
+  double scale;
+  int32_t mode;             // 0 gradient and log K at B; 1 L leapfrog updates of (B, eta, G); 2 transition
+  int32_t L;
+  double h, eps;            // half step, full step (modes 1, 2)
+  void* B; void* G; void* eta;   // eta: mode 1
+  double* logpost;
+  // mode 2: as StartArgs and AcceptArgs; ctr, if given, is advanced at the end
+  int32_t draw, chain;
+  const double* normals; const double* replay_u; const double* inv_temp;
+  uint64_t seed;
+  int64_t iter, t, n_rec;
+  int64_t* ctr;
+  void* sample;
+  int32_t* accepted; double* H; int32_t* divergent;
+};
+
 struct FinalArgs {
   const double* lpart; int32_t nl;
   const double* ppart; int32_t np;
@@ -230,6 +252,10 @@ template <typename T> hipError_t launch_epilogue(const EpiArgs& a, int nwg, hipS
 template <typename T> hipError_t launch_start(const StartArgs& a, int nwg, hipStream_t s);
 template <typename T> hipError_t launch_accept(const AcceptArgs& a, int nwg, hipStream_t s);
 hipError_t launch_final(const FinalArgs& a, hipStream_t s);
+
+// Does one workgroup take a problem of these sizes (n, p, K; p x K state)?
+bool tiny_fits(int64_t n, int64_t p, int K, bool f64);
+template <typename T> hipError_t launch_tiny(const TinyArgs& a, hipStream_t s);
 
 template <typename T> int wide_chunk_cols();
 int wide_grad_groups(int64_t p, bool f64);
