@@ -245,7 +245,8 @@ hmc_status hmc_sample(const hmc_problem* prob, void* B, void* G, double* logpost
 
 /* Graph plans: one HMC iteration of hmc_sample (momentum draw, L leapfrog updates,
  * Metropolis test, records) captured once as a HIP graph and replayed, so a run of many
- * iterations costs one graph launch per iteration instead of one launch per kernel. The
+ * iterations costs one graph launch per iteration instead of one launch per kernel (a small
+ * problem's iteration is one kernel, which a replay launches itself). The
  * state, arguments and workspace given at creation are baked into the graph and must stay
  * valid until hmc_plan_destroy. The iteration index and the record slot come from a
  * counter in the workspace, set to args->first_iter before the plan's first launch and
@@ -394,7 +395,9 @@ hmc_status hmc_stream_read(const void* buf, size_t bytes, int32_t reps, void* si
  * stream, from a pool of `capacity` pairs the library creates (host-side event objects; no
  * device memory). A pass that only overwrites workspace runs `repeat` times (1..64) back to
  * back inside its pair, which spreads the cost of recording the events; the wide-p pass
- * with one row slice updates the chain state itself and always runs once. Launches beyond
+ * with one row slice updates the chain state itself and always runs once, and so do the updates
+ * of a small problem, which run in one launch per leapfrog call or transition, whose time counts
+ * as that of L passes. Launches beyond
  * the capacity are not timed. hmc_profile_end waits for the recorded events, writes the
  * number of timed pairs and the mean / min / max duration of one launch in microseconds
  * (each pair's time over its launches), and releases the pool. A timed run with

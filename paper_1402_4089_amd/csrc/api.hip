@@ -167,7 +167,7 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
   if (L->hilo != (tu.path == 3) && tu.path != 0)
     return fail(HMC_ERR_ARG, "tuning.path %d does not fit X format %d (path 3 is the bf16 formats' only path)",
                 tu.path, pr->xfmt);
-  L->tiny = !L->hilo && tu.path == 0 && tiny_fits(pr->n, pr->p, pr->K, L->f64);
+  L->tiny = !L->hilo && tu.path == 0 && tiny_fits(pr->n, pr->p, pr->K, pr->pin_last_class != 0, L->f64);
   if (tu.path == 1 || tu.path == 0) {
     const bool ruled = tu.waves == 0 && tu.mb == 0;
     bool ok;
@@ -558,6 +558,16 @@ hmc_status do_leapfrog(const hmc_problem* pr, const Layout& L, void* B, void* et
   return hip_status(launch_final(fa, s), "log-posterior final sum");
 }
 
+TinyArgs tiny_transition(const hmc_problem* pr, void* B, void* G, double* logpost, const hmc_sample_args* ar, int64_t t,
+                         int64_t* ctr) {
+  TinyArgs a = tiny_args(pr, B, G, logpost, ar->eps, ar->L, 2);
+  a.draw = ar->replay_normals ? 1 : 2; a.normals = ar->replay_normals; a.replay_u = ar->replay_uniforms;
+  a.inv_temp = ar->inv_temperature; a.seed = ar->seed; a.chain = ar->chain;
+  a.iter = (int64_t)ar->first_iter + t; a.t = t; a.n_rec = ar->n_iter; a.ctr = ctr;
+  a.sample = ar->samples; a.accepted = ar->accepted; a.H = ar->H; a.divergent = ar->divergent;
+  return a;
+}
+
 // One HMC iteration (momentum draw, L leapfrog updates, Metropolis test) enqueued on s.
 // Record slot t and iteration first_iter + t come from the arguments, or, when ctr is a
 // device counter {iteration, first iteration}, from device memory at run time (graphs); the
@@ -567,11 +577,7 @@ hmc_status enqueue_iteration(const hmc_problem* pr, const Layout& L, void* B, vo
                              double* logpost, const hmc_sample_args* ar, void* ws, hipStream_t s,
                              int64_t t, int64_t* ctr) {
   if (L.tiny) {
-    TinyArgs a = tiny_args(pr, B, G, logpost, ar->eps, ar->L, 2);
-    a.draw = ar->replay_normals ? 1 : 2; a.normals = ar->replay_normals; a.replay_u = ar->replay_uniforms;
-    a.inv_temp = ar->inv_temperature; a.seed = ar->seed; a.chain = ar->chain;
-    a.iter = (int64_t)ar->first_iter + t; a.t = t; a.n_rec = ar->n_iter; a.ctr = ctr;
-    a.sample = ar->samples; a.accepted = ar->accepted; a.H = ar->H; a.divergent = ar->divergent;
+    const TinyArgs a = tiny_transition(pr, B, G, logpost, ar, t, ctr);
     return timed_launch(s, false, [&] { return hip_status(launch_tiny<T>(a, s), "one-workgroup transition"); }, ar->L);
   }
   void* eta = at<void>(ws, L.off_eta);
@@ -1169,8 +1175,11 @@ hmc_status hmc_batch_autotune(const hmc_problem* probs, int32_t n_prob, int32_t 
 
 // ---------------------------------------------------------------------------------------
 // Plans: one HMC iteration captured as a HIP graph and replayed; the iteration index
-// lives in the workspace counter, advanced by the graph's last node.
+// lives in the workspace counter, advanced by the graph's last node. A small problem's
+// iteration is one kernel, which a replay launches itself (a graph of one node costs more).
 struct hmc_plan {
+  bool direct = false, f64 = false;
+  TinyArgs tiny{};
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   int64_t* ctr = nullptr;
@@ -1228,6 +1237,13 @@ hmc_status hmc_plan_create(hmc_plan** plan, const hmc_problem* prob, void* B, vo
                args->inv_temperature;
   const hmc_sample_args ar = *args;
   const hmc_problem pr = *prob;
+  if (L.tiny) {
+    P->direct = true;
+    P->f64 = L.f64;
+    P->tiny = tiny_transition(&pr, B, G, logpost, &ar, 0, P->ctr);
+    *plan = P;
+    return HMC_OK;
+  }
   hmc_status st = capture(P, [&](hipStream_t cs) -> hmc_status {
     return L.f64 ? enqueue_iteration<double>(&pr, L, B, G, logpost, &ar, ws, cs, 0, P->ctr)
                  : enqueue_iteration<float>(&pr, L, B, G, logpost, &ar, ws, cs, 0, P->ctr);
@@ -1271,7 +1287,7 @@ hmc_status hmc_plan_create_batched(hmc_plan** plan, const hmc_problem* probs, in
 }
 
 hmc_status hmc_plan_launch(hmc_plan* plan, int32_t n_iter, void* stream) {
-  if (!plan || !plan->exec) return fail(HMC_ERR_ARG, "plan is NULL or was not created");
+  if (!plan || !(plan->exec || plan->direct)) return fail(HMC_ERR_ARG, "plan is NULL or was not created");
   if (n_iter < 0) return fail(HMC_ERR_ARG, "n_iter = %d must be >= 0", n_iter);
   if (plan->bounded && plan->launched + n_iter > plan->n_rec)
     return fail(HMC_ERR_ARG, "%lld + %d iterations exceed the %lld the plan's records hold",
@@ -1281,7 +1297,10 @@ hmc_status hmc_plan_launch(hmc_plan* plan, int32_t n_iter, void* stream) {
     HMC_TRY(hip_status(launch_counter(plan->ctr, plan->first_iter, 0, s), "iteration counter"));
     plan->started = true;
   }
-  for (int i = 0; i < n_iter; ++i) HMC_TRY(hip_status(hipGraphLaunch(plan->exec, s), "hipGraphLaunch"));
+  for (int i = 0; i < n_iter; ++i) {
+    if (!plan->direct) HMC_TRY(hip_status(hipGraphLaunch(plan->exec, s), "hipGraphLaunch"));
+    else HMC_TRY(hip_status(plan->f64 ? launch_tiny<double>(plan->tiny, s) : launch_tiny<float>(plan->tiny, s), "one-workgroup transition"));
+  }
   plan->launched += n_iter;
   return HMC_OK;
 }

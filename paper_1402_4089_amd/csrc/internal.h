@@ -253,8 +253,8 @@ template <typename T> hipError_t launch_start(const StartArgs& a, int nwg, hipSt
 template <typename T> hipError_t launch_accept(const AcceptArgs& a, int nwg, hipStream_t s);
 hipError_t launch_final(const FinalArgs& a, hipStream_t s);
 
-// Does one workgroup take a problem of these sizes (n, p, K; p x K state)?
-bool tiny_fits(int64_t n, int64_t p, int K, bool f64);
+// Does one workgroup take a problem of these sizes?
+bool tiny_fits(int64_t n, int64_t p, int K, bool pin, bool f64);
 template <typename T> hipError_t launch_tiny(const TinyArgs& a, hipStream_t s);
 
 template <typename T> int wide_chunk_cols();

@@ -5,10 +5,12 @@
 // kernels per update take 4.3 us each, which is what a launch costs, not the work: a
 // transition of ten updates was 23 launches and 99 us. Here an update is three phases between
 // workgroup barriers: a thread per row of X forms the row's logits, softmax and residuals; a
-// thread per gradient element and row group sums x r over its rows in float64; a thread per
-// element adds the prior and applies the kicks and the drift. Latency bounds it (about 3 us per
-// update: the float64 exponentials and the serial sums), so it is used while a thread has few
-// rows and terms (tiny_fits).
+// thread per column of X and group of rows sums x r over its rows in float64 for every free
+// class; a thread per element adds the prior and applies the kicks and the drift. LDS reads and
+// the latency of the float64 functions bound it, so it is used while a thread has one row, one
+// element and few terms (tiny_fits). That transition now takes 45 us, 3.7 per update (timed with
+// phases left out: logits 1.3, softmax 1.1, gradient 1.4 of 4.9 in a form with a thread per
+// gradient element, whose LDS reads were twice as many), and one gradient 9.6.
 //
 // A row's logits are formed in the order of the row-tile kernel's matrix instructions (blocks of
 // 16 columns, in a block columns t, 4 + t, 8 + t, 12 + t for t = 0 .. 3, the blocks' sums added in
@@ -25,29 +27,29 @@ namespace {
 using namespace dev;
 
 constexpr size_t kTinyLds = 150 * 1024;
+constexpr int kTinyGroups = 16;                    // row groups of the gradient at most
 
-// LDS sections of a problem, in bytes from the start (each 16-byte aligned).
+// LDS sections of a problem, in bytes from the start (each 16-byte aligned). fp: free classes
+// (K, or K - 1 with the pinned class) padded to a power of two.
 struct TinyLayout {
-  size_t x, b, pos, mom, grad, res, red, total;
+  size_t x, b, res, red, total;
   int pitch;                                       // elements between rows of X, odd
+  int groups;                                      // row groups of the gradient
 };
-__host__ __device__ inline TinyLayout tiny_layout(int n, int p, int K, int kp, int threads, size_t ts) {
+__host__ __device__ inline TinyLayout tiny_layout(int n, int p, int fp, int threads, size_t ts) {
   TinyLayout l;
   const auto up = [](size_t v) { return (v + 15) / 16 * 16; };
-  const size_t pk = (size_t)p * K;
   l.pitch = p | 1;
+  l.groups = threads / p < kTinyGroups ? threads / p : kTinyGroups;
   l.x = 0;
   l.b = up(l.x + (size_t)n * l.pitch * ts);
-  l.pos = up(l.b + (size_t)p * kp * ts);
-  l.mom = up(l.pos + pk * ts);
-  l.grad = up(l.mom + pk * ts);
-  l.res = up(l.grad + pk * ts);
-  l.red = up(l.res + (size_t)n * K * ts);
-  l.total = up(l.red + (pk > (size_t)threads ? pk : (size_t)threads) * 8);
+  l.res = up(l.b + (size_t)p * fp * ts);
+  l.red = up(l.res + (size_t)n * fp * ts);
+  l.total = up(l.red + (size_t)l.groups * p * fp * 8);
   return l;
 }
-int class_pad(int K) { return K == 1 ? 1 : K <= 4 ? 4 : K <= 8 ? 8 : 16; }
-int tiny_threads(int64_t n) { return n <= 512 ? 512 : 1024; }
+int class_pad(int f) { return f <= 1 ? 1 : f <= 2 ? 2 : f <= 4 ? 4 : f <= 8 ? 8 : 16; }
+int tiny_threads(int64_t n, int64_t pk) { return n <= 512 && pk <= 512 ? 512 : 1024; }
 
 // Sum over the workgroup in a fixed order, the same in every thread.
 template <int TH> __device__ double block_sum(double v, double* sh) {
@@ -61,55 +63,50 @@ template <int TH> __device__ double block_sum(double v, double* sh) {
   return s;
 }
 
-// Sum of KP values in the order of a 16-lane DPP reduction (pairs, quads, halves).
-template <typename T, int KP> __device__ __forceinline__ T tree(const T (&e)[KP]) {
-  if constexpr (KP == 1) return e[0];
-  T v[KP];
+// Sum of N values (a power of two) in the order of a 16-lane DPP reduction.
+template <typename T, int N> __device__ __forceinline__ T tree(T (&v)[N]) {
 #pragma unroll
-  for (int k = 0; k < KP; ++k) v[k] = e[k];
+  for (int h = 1; h < N; h *= 2)
 #pragma unroll
-  for (int h = 1; h < KP; h *= 2)
-#pragma unroll
-    for (int k = 0; k < KP; k += 2 * h) v[k] += v[k + h];
+    for (int k = 0; k < N; k += 2 * h) v[k] += v[k + h];
   return v[0];
 }
 
-template <typename T, int KP, int TH>
+template <typename T, int FP, int TH>
 __global__ __launch_bounds__(TH) void tiny_kernel(TinyArgs a) {
+  constexpr int KP = 2 * FP < 16 ? 2 * FP : 16;        // padded classes, the pinned one among them
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double sh[TH / 64];
   const int tid = threadIdx.x;
   const int n = (int)a.n, p = a.p, K = a.K, pk = p * K;
-  const TinyLayout l = tiny_layout(n, p, K, KP, TH, sizeof(T));
+  const int F = a.pin ? K - 1 : K;
+  const TinyLayout l = tiny_layout(n, p, FP, TH, sizeof(T));
   T* xs = reinterpret_cast<T*>(smem + l.x);            // [n][pitch]
-  T* bs = reinterpret_cast<T*>(smem + l.b);            // [p][KP] position, zero past the free classes
-  T* pos = reinterpret_cast<T*>(smem + l.pos);         // [p][K]
-  T* mom = reinterpret_cast<T*>(smem + l.mom);
-  T* grad = reinterpret_cast<T*>(smem + l.grad);
-  T* res = reinterpret_cast<T*>(smem + l.res);         // [n][K]
-  double* red = reinterpret_cast<double*>(smem + l.red);
+  T* bs = reinterpret_cast<T*>(smem + l.b);            // [p][FP] position, zero past the free classes
+  T* res = reinterpret_cast<T*>(smem + l.res);         // [n][FP] residuals of the free classes
+  double* red = reinterpret_cast<double*>(smem + l.red);   // [groups][p][FP]
   const T* X = static_cast<const T*>(a.X);
-  T* B = static_cast<T*>(a.B);
-  T* G = static_cast<T*>(a.G);
-  T* eta = static_cast<T*>(a.eta);
   const T h = (T)a.h, eps = (T)a.eps;
-  auto pinned = [&](int e) { return a.pin && e % K == K - 1; };
-  auto put = [&](int e, T v) {                         // position of element e
-    pos[e] = v;
-    bs[e / K * KP + e % K] = pinned(e) ? T(0) : v;
-  };
 
+  // this thread's element of the state (row ej, class ek), its row of X and its share of the gradient
+  const bool elem = tid < pk;
+  const int ej = elem ? tid / K : 0, ek = elem ? tid - ej * K : 0;
+  const bool pin = a.pin && ek == K - 1, free = elem && !pin;
+  const bool row = tid < n;
+  const int gq = tid / p, gj = tid - gq * p;           // gradient: column gj, rows gq, gq + groups, ..
+  const int yi = row ? a.y[tid] : 0;
+  const T b0 = elem ? static_cast<const T*>(a.B)[tid] : T(0);
+  const T g0 = elem && a.mode != 0 ? static_cast<const T*>(a.G)[tid] : T(0);
   {
     // element tid, tid + TH, .. of the rows, row and column stepped without a division
     const int dr = TH / p, dc = TH - dr * p;
-    int r = tid / p, c = tid - r * p;
+    int r = gq, c = gj;
     while (r < n) {
       T v[8];
-      int rr[8], cc[8];
+      int at[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        rr[u] = r;
-        cc[u] = c;
+        at[u] = r < n ? r * l.pitch + c : -1;
         v[u] = r < n ? X[(int64_t)r * a.ldx + c] : T(0);
         c += dc;
         r += dr + (c >= p);
@@ -117,145 +114,148 @@ __global__ __launch_bounds__(TH) void tiny_kernel(TinyArgs a) {
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (rr[u] < n) xs[rr[u] * l.pitch + cc[u]] = v[u];
+        if (at[u] >= 0) xs[at[u]] = v[u];
     }
   }
-  for (int i = tid; i < p * KP; i += TH) bs[i] = T(0);
-  __syncthreads();
+  for (int i = tid; i < p * FP; i += TH) bs[i] = T(0);
+  for (int i = tid; i < n * FP; i += TH) res[i] = T(0);
 
   // start of the trajectory: momentum, opening half kick and drift (equations (hmc1) and the
   // position step)
   const int64_t iter = a.ctr ? a.ctr[0] : a.iter;
   const int64_t t = a.ctr ? a.ctr[0] - a.ctr[1] : a.t;
   const bool rec = t >= 0 && t < a.n_rec;
-  double ke0 = 0.0;
-  for (int e = tid; e < pk; e += TH) {
-    T bt = B[e];
-    if (a.mode != 0) {
-      T ev;
-      if (a.mode == 1) {
-        ev = eta[e];
-      } else {
-        const double xi = a.draw == 1 && rec ? a.normals[t * pk + e] : philox_normal(a.seed, a.chain, iter, e);
-        ev = pinned(e) ? T(0) : (T)xi;
-        ke0 += 0.5 * (double)ev * (double)ev;
-      }
-      ev = ev + h * G[e];
-      bt = pinned(e) ? T(0) : bt + eps * ev;
-      mom[e] = ev;
+  double ke0 = 0.0, ke1 = 0.0, pr = 0.0, logk = 0.0;
+  T pos = b0, mom = T(0), grad = T(0);
+  if (elem && a.mode != 0) {
+    if (a.mode == 1) {
+      mom = static_cast<const T*>(a.eta)[tid];
+    } else {
+      const double xi = a.draw == 1 && rec ? a.normals[t * pk + tid] : philox_normal(a.seed, a.chain, iter, tid);
+      mom = pin ? T(0) : (T)xi;
+      ke0 = 0.5 * (double)mom * (double)mom;
     }
-    put(e, bt);
+    mom = mom + h * g0;
+    pos = pin ? T(0) : b0 + eps * mom;
   }
   __syncthreads();
+  if (free) bs[ej * FP + ek] = pos;
+  // the pinned class's logit: zero, or a NaN in a row that holds an infinity or a NaN
+  T zpin = T(0);
+  if (row && a.pin)
+    for (int j = 0; j < p; ++j) zpin = fma(xs[tid * l.pitch + j], T(0), zpin);
+  __syncthreads();
 
-  // elements of the gradient and row groups: threads e + pk q sum rows q, q + ngrp, ..
-  const int ngrp = pk < TH ? TH / pk : 1;
-  double logk = 0.0, ke1 = 0.0;
   const int steps = a.mode == 0 ? 1 : a.L;
   for (int st = 1; st <= steps; ++st) {
     double lacc = 0.0;
-    for (int i = tid; i < n; i += TH) {
-      const T* x = xs + i * l.pitch;
-      T z[KP];
-      for (int b0 = 0; b0 < p; b0 += 16) {
-        T zb[KP];
+    if (row) {
+      const T* x = xs + tid * l.pitch;
+      T z[FP];
+      for (int c0 = 0; c0 < p; c0 += 16) {
+        T zb[FP];
 #pragma unroll
-        for (int k = 0; k < KP; ++k) zb[k] = T(0);
+        for (int k = 0; k < FP; ++k) zb[k] = T(0);
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-          const int j = b0 + 4 * (q & 3) + (q >> 2);
+          const int j = c0 + 4 * (q & 3) + (q >> 2);
           if (j < p) {
             const T xv = x[j];
 #pragma unroll
-            for (int k = 0; k < KP; ++k) zb[k] = fma(xv, bs[j * KP + k], zb[k]);
+            for (int k = 0; k < FP; ++k) zb[k] = fma(xv, bs[j * FP + k], zb[k]);
           }
         }
 #pragma unroll
-        for (int k = 0; k < KP; ++k) z[k] = b0 == 0 ? zb[k] : z[k] + zb[k];
+        for (int k = 0; k < FP; ++k) z[k] = c0 == 0 ? zb[k] : z[k] + zb[k];
       }
-      const int yi = a.y[i];
-      if constexpr (KP == 1) {
+      bool done = false;
+      if constexpr (FP == 1) {
         if (a.link == 1) {
           const T mu = dev_exp(z[0]);
-          res[i] = T(yi) - mu;
-          lacc += (double)yi * (double)z[0] - (double)mu;
-        } else {
+          res[tid] = T(yi) - mu;
+          lacc = (double)yi * (double)z[0] - (double)mu;
+          done = true;
+        } else if (a.link == 2) {
           const T s = yi == 1 ? T(1) : T(-1);
           T ratio;
-          double lp;
-          probit_row(s * z[0], ratio, lp);
-          res[i] = s * ratio;
-          lacc += lp;
+          probit_row(s * z[0], ratio, lacc);
+          res[tid] = s * ratio;
+          done = true;
         }
-      } else {
-        T mx = -INFINITY;
+      }
+      if (!done) {
+        T mx = a.pin ? fmax((T)-INFINITY, zpin) : (T)-INFINITY;
 #pragma unroll
-        for (int k = 0; k < KP; ++k)
-          if (k < K) mx = fmax(mx, z[k]);
-        T ex[KP];
-#pragma unroll
-        for (int k = 0; k < KP; ++k) ex[k] = k < K ? dev_exp(z[k] - mx) : T(0);
-        const T se = tree<T, KP>(ex);
-        const T inv = dev_rcp(se), lse_shift = dev_log(se);
+        for (int k = 0; k < FP; ++k)
+          if (k < F) mx = fmax(mx, z[k]);
+        T ex[KP], sum[KP];
 #pragma unroll
         for (int k = 0; k < KP; ++k) {
-          if (k < K) res[i * K + k] = (k == yi ? T(1) : T(0)) - ex[k] * inv;
-          lacc += k == yi ? (double)((z[k] - mx) - lse_shift) : 0.0;
+          ex[k] = T(0);
+          if (k < K) ex[k] = dev_exp((k < FP && k < F ? z[k < FP ? k : 0] : zpin) - mx);
+          sum[k] = ex[k];
         }
+        const T se = tree<T, KP>(sum);
+        const T inv = dev_rcp(se), lse_shift = dev_log(se);
+        T zy = zpin;                                   // the label's logit
+#pragma unroll
+        for (int k = 0; k < FP; ++k)
+          if (k < F) {
+            res[tid * FP + k] = (k == yi ? T(1) : T(0)) - ex[k] * inv;
+            zy = k == yi ? z[k] : zy;
+          }
+        lacc = (double)((zy - mx) - lse_shift);
       }
     }
     __syncthreads();
-    for (int e = tid; e < pk * ngrp; e += TH) {
-      const int el = e % pk, j = el / K, k = el % K;
-      double s[4] = {0.0, 0.0, 0.0, 0.0};
-      int i = e / pk;
-      for (; i + 3 * ngrp < n; i += 4 * ngrp) {
+    if (gq < l.groups) {
+      double s[FP];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          s[u] = fma((double)xs[(i + u * ngrp) * l.pitch + j], (double)res[(i + u * ngrp) * K + k], s[u]);
+      for (int k = 0; k < FP; ++k) s[k] = 0.0;
+#pragma unroll 4
+      for (int i = gq; i < n; i += l.groups) {
+        const double xv = (double)xs[i * l.pitch + gj];
+#pragma unroll
+        for (int k = 0; k < FP; ++k) s[k] = fma(xv, (double)res[i * FP + k], s[k]);
       }
-      for (; i < n; i += ngrp) s[0] = fma((double)xs[i * l.pitch + j], (double)res[i * K + k], s[0]);
-      red[e] = ((s[0] + s[1]) + s[2]) + s[3];
+#pragma unroll
+      for (int k = 0; k < FP; ++k) red[(gq * p + gj) * FP + k] = s[k];
     }
     __syncthreads();
     const bool last = st == steps;
-    double pr = 0.0;
-    for (int e = tid; e < pk; e += TH) {
-      double gsum = red[e];
-      for (int q = 1; q < ngrp; ++q) gsum += red[q * pk + e];
-      const bool pin = pinned(e);
-      const T bt = pos[e];
-      const double b = (double)bt;
-      const T gt = pin ? T(0) : (T)(gsum + prior_grad(b, a.prior, a.scale));
-      if (last) {
-        grad[e] = gt;
-        pr += pin ? 0.0 : prior_logd(b, a.prior, a.scale);
+    if (elem) {
+      double gsum = 0.0;
+      if (free) {
+#pragma unroll 8
+        for (int q = 0; q < l.groups; ++q) gsum += red[(q * p + ej) * FP + ek];
       }
+      const double b = (double)pos;
+      grad = pin ? T(0) : (T)(gsum + prior_grad(b, a.prior, a.scale));
+      if (last) pr = pin ? 0.0 : prior_logd(b, a.prior, a.scale);
       if (a.mode != 0) {
-        T ev = mom[e] + h * gt;                        // closing half kick, equation (hmc3)
+        mom = mom + h * grad;                          // closing half kick, equation (hmc3)
         if (last) {
-          ke1 += 0.5 * (double)ev * (double)ev;
+          ke1 = 0.5 * (double)mom * (double)mom;
         } else {
-          ev = ev + h * gt;                            // opening half kick of the next update
-          put(e, pin ? T(0) : bt + eps * ev);          // full position step
+          mom = mom + h * grad;                        // opening half kick of the next update
+          pos = pin ? T(0) : pos + eps * mom;          // full position step
+          if (free) bs[ej * FP + ek] = pos;
         }
-        mom[e] = ev;
       }
     }
     if (last) logk = block_sum<TH>(lacc + pr, sh);
     __syncthreads();
   }
 
-  if (a.mode == 0) {
-    for (int e = tid; e < pk; e += TH) G[e] = grad[e];
-    if (tid == 0) *a.logpost = logk;
-    return;
-  }
-  if (a.mode == 1) {
-    for (int e = tid; e < pk; e += TH) {
-      B[e] = pos[e];
-      eta[e] = mom[e];
-      G[e] = grad[e];
+  T* B = static_cast<T*>(a.B);
+  T* G = static_cast<T*>(a.G);
+  if (a.mode != 2) {
+    if (elem) {
+      G[tid] = grad;
+      if (a.mode == 1) {
+        B[tid] = pos;
+        static_cast<T*>(a.eta)[tid] = mom;
+      }
     }
     if (tid == 0) *a.logpost = logk;
     return;
@@ -270,16 +270,12 @@ __global__ __launch_bounds__(TH) void tiny_kernel(TinyArgs a) {
   const bool finite = isfinite(H1);
   const bool acc = finite && (log(u) < (H0 - H1) * it);
   __syncthreads();                                     // every thread has read log K and the counter
-  for (int e = tid; e < pk; e += TH) {
-    T bnew;
+  if (elem) {
     if (acc) {
-      bnew = pos[e];
-      B[e] = bnew;
-      G[e] = grad[e];
-    } else {
-      bnew = B[e];
+      B[tid] = pos;
+      G[tid] = grad;
     }
-    if (a.sample && rec) static_cast<T*>(a.sample)[t * pk + e] = bnew;
+    if (a.sample && rec) static_cast<T*>(a.sample)[t * pk + tid] = acc ? pos : b0;
   }
   if (tid == 0) {
     *a.logpost = acc ? logk : logk0;
@@ -292,29 +288,30 @@ __global__ __launch_bounds__(TH) void tiny_kernel(TinyArgs a) {
   }
 }
 
-template <typename T, int KP, int TH>
+template <typename T, int FP, int TH>
 hipError_t launch_one(const TinyArgs& a, size_t lds, hipStream_t s) {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tiny_kernel<T, KP, TH>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tiny_kernel<T, FP, TH>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((tiny_kernel<T, KP, TH>), dim3(1), dim3(TH), lds, s, a);
+  hipLaunchKernelGGL((tiny_kernel<T, FP, TH>), dim3(1), dim3(TH), lds, s, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-bool tiny_fits(int64_t n, int64_t p, int K, bool f64) {
-  if (n > 1024 || p > 256 || K > 16 || n * p * K > (int64_t)1 << 16) return false;
-  return tiny_layout((int)n, (int)p, K, class_pad(K), tiny_threads(n), f64 ? 8 : 4).total <= kTinyLds;
+bool tiny_fits(int64_t n, int64_t p, int K, bool pin, bool f64) {
+  if (n > 1024 || p > 256 || K > 16 || p * K > 1024 || n * p * K > (int64_t)1 << 16) return false;
+  const int th = tiny_threads(n, p * K);
+  return tiny_layout((int)n, (int)p, class_pad(pin ? K - 1 : K), th, f64 ? 8 : 4).total <= kTinyLds;
 }
 
 template <typename T>
 hipError_t launch_tiny(const TinyArgs& a, hipStream_t s) {
-  const int kp = class_pad(a.K), th = tiny_threads(a.n);
-  const size_t lds = tiny_layout((int)a.n, a.p, a.K, kp, th, sizeof(T)).total;
-#define HMC_TINY(KP_)                                                                        \
-  if (kp == KP_) return th == 512 ? launch_one<T, KP_, 512>(a, lds, s) : launch_one<T, KP_, 1024>(a, lds, s);
-  HMC_TINY(1) HMC_TINY(4) HMC_TINY(8) HMC_TINY(16)
+  const int fp = class_pad(a.pin ? a.K - 1 : a.K), th = tiny_threads(a.n, (int64_t)a.p * a.K);
+  const size_t lds = tiny_layout((int)a.n, a.p, fp, th, sizeof(T)).total;
+#define HMC_TINY(FP_)                                                                        \
+  if (fp == FP_) return th == 512 ? launch_one<T, FP_, 512>(a, lds, s) : launch_one<T, FP_, 1024>(a, lds, s);
+  HMC_TINY(1) HMC_TINY(2) HMC_TINY(4) HMC_TINY(8) HMC_TINY(16)
 #undef HMC_TINY
   return hipErrorInvalidValue;
 }
