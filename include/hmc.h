@@ -280,9 +280,8 @@ hmc_status hmc_plan_destroy(hmc_plan* plan);
 
 /* Work decomposition of the batched kernels: rows per gradient row slice (a multiple of
  * 32, >= 1024) and persistent workgroups of the logits and gradient kernels (64..65536);
- * 0 selects the default (4096 rows, 1024 or 2048 for a small batch; a workgroup per item, up to
- * 16384). hmc_batch_autotune measures a set
- * of candidates on the device and returns the fastest. */
+ * 0 selects the default (4096 rows; a workgroup per item, up to 16384). hmc_batch_autotune
+ * measures a set of candidates on the device and returns the fastest. */
 typedef struct {
   int32_t rows_per_slice;
   int32_t grid;

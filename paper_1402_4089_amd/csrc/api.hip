@@ -638,22 +638,12 @@ hmc_status check_sample_args(const hmc_sample_args* args) {
 // ceil(max K / 16) class blocks (the batch's `group`), chains x group <= 4.
 
 constexpr int kBatchMinRows = 1024;       // smallest gradient row slice the workspace holds
-// Default decomposition: 4096 rows per gradient slice, fewer while a batch has less than one
-// gradient item per compute unit (4 problems of n ~ U[1k, 50k], p ~ U[64, 2048], 4 chains: 255 us
-// per update with 4096 rows, 239 with 1024; 16 problems: 643 and 663), and a workgroup per item,
-// which lets the dispatcher balance the uneven items (16 problems: 660 us per update with 2048
-// workgroups, 643 with one per item; 48 problems, hi-only: 1262 and 1237).
+// Default decomposition: 4096 rows per gradient slice, and a workgroup per item, which lets the
+// dispatcher balance the uneven items (16 problems of n ~ U[1k, 50k], p ~ U[64, 2048], 4 chains:
+// 660 us per update with 2048 workgroups, 643 with one per item; 48 problems, hi-only: 1262 and
+// 1237).
 constexpr int kBatchDefaultRows = 4096;
 constexpr int kBatchDefaultGrid = 16384;
-int batch_default_rows(const hmc_problem* probs, int32_t n_prob) {
-  int rows = kBatchDefaultRows;
-  for (;; rows /= 2) {
-    int64_t items = 0;
-    for (int b = 0; b < n_prob; ++b)
-      items += (probs[b].n + rows - 1) / rows * ((probs[b].p + kGradCols - 1) / kGradCols);
-    if (items >= 256 || rows <= kBatchMinRows) return rows;
-  }
-}
 
 struct BatchLayout {
   int nprob = 0, chains = 0, group = 1;   // group: 16-class blocks per chain
@@ -705,7 +695,7 @@ hmc_status check_batch(const hmc_problem* probs, int32_t n_prob, int32_t chains)
 hmc_status make_batch_layout(const hmc_problem* probs, int32_t n_prob, int32_t chains, int rows,
                              int grid, BatchLayout* B) {
   HMC_TRY(check_batch(probs, n_prob, chains));
-  if (rows == 0) rows = batch_default_rows(probs, n_prob);
+  if (rows == 0) rows = kBatchDefaultRows;
   if (grid == 0) grid = kBatchDefaultGrid;
   if (rows < kBatchMinRows || rows % 32) return fail(HMC_ERR_ARG, "rows_per_slice = %d must be a multiple of 32, >= %d", rows, kBatchMinRows);
   if (grid < 64 || grid > 65536) return fail(HMC_ERR_ARG, "grid = %d must be in [64, 65536]", grid);
