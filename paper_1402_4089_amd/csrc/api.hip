@@ -206,14 +206,14 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
   L->hl_logits_wg = L->hl_cols = L->hl_nsplit = 0;
   L->hl_rps = 0;
   if (L->hilo) {
-    // logits: row blocks of kHiloRows rows; gradient: kGradCols-column blocks times row
+    // logits: row blocks of kHiloRows rows; gradient: 256-column blocks times row
     // slices, as many slices as give about 2048 items of 128 columns
     const int64_t rows = kHiloRows;
     const int64_t nrb = (pr->n + rows - 1) / rows;
     if (tu.grid > 65536) return fail(HMC_ERR_ARG, "tuning.grid = %d must be <= 65536", tu.grid);
     const int64_t lwg = tu.grid ? tu.grid : 2048;
     L->hl_logits_wg = (int)(nrb < lwg ? nrb : lwg);
-    L->hl_cols = (int)((pr->p + kGradCols - 1) / kGradCols);
+    L->hl_cols = (int)((pr->p + grad_cols(8) - 1) / grad_cols(8));
     if (tu.rows_per_slice) {
       if (tu.rows_per_slice % 32) return fail(HMC_ERR_ARG, "tuning.rows_per_slice = %d must be a multiple of 32", tu.rows_per_slice);
       L->hl_rps = std::min<int64_t>(tu.rows_per_slice, (pr->n + 31) / 32 * 32);
@@ -645,9 +645,25 @@ constexpr int kBatchMinRows = 1024;       // smallest gradient row slice the wor
 constexpr int kBatchDefaultRows = 4096;
 constexpr int kBatchDefaultGrid = 16384;
 
+// Waves of a gradient workgroup: 8 (256 columns, the least residual traffic), fewer while a batch
+// has less than 64 gradient items, one for every fourth compute unit (shorter row slices would
+// give more items too, but change the order of the row sums). Measured per update with 8 / 4 / 2
+// waves, n ~ U[1k, 50k], p ~ U[64, 2048], 4 chains: 1 problem 141 / 122 / 110 us, 2 problems 171 /
+// 149 / 160, 4 problems 256 / 278 / 274, 16 problems 642 / 685 / 727.
+int batch_grad_waves(const hmc_problem* probs, int32_t n_prob, int rows) {
+  int w = 8;
+  for (;; w /= 2) {
+    int64_t items = 0;
+    for (int b = 0; b < n_prob; ++b)
+      items += (probs[b].n + rows - 1) / rows * ((probs[b].p + grad_cols(w) - 1) / grad_cols(w));
+    if (items >= 64 || w == 2) return w;
+  }
+}
+
 struct BatchLayout {
   int nprob = 0, chains = 0, group = 1;   // group: 16-class blocks per chain
   bool lo = false;
+  int gwaves = 8;                         // waves of a gradient workgroup
   int rows = kBatchDefaultRows, grid = kBatchDefaultGrid;
   std::vector<BatchProb> table;           // entry t describes problem order[t]
   std::vector<int32_t> order;
@@ -713,6 +729,7 @@ hmc_status make_batch_layout(const hmc_problem* probs, int32_t n_prob, int32_t c
   for (auto& f : B->first) f.assign(n_prob + 1, 0);
   int64_t bytes = 0, slices = 0;
   for (int b = 0; b < n_prob; ++b) bytes += plane_bytes(probs[b]);
+  B->gwaves = batch_grad_waves(probs, n_prob, rows);
   size_t off = 0;
   B->off_table = off; off = align_up(off + sizeof(BatchProb) * n_prob);
   B->off_first = off; off = align_up(off + 5 * sizeof(int32_t) * (n_prob + 1));
@@ -728,7 +745,7 @@ hmc_status make_batch_layout(const hmc_problem* probs, int32_t n_prob, int32_t c
     P.n = pr.n; P.p = (int32_t)pr.p; P.K = pr.K;
     P.prior = pr.prior; P.pin = pr.pin_last_class; P.scale = pr.prior_scale;
     P.nrb = (int32_t)((pr.n + rb_rows - 1) / rb_rows);
-    P.gcols = (int32_t)((pr.p + kGradCols - 1) / kGradCols);
+    P.gcols = (int32_t)((pr.p + grad_cols(B->gwaves) - 1) / grad_cols(B->gwaves));
     P.rps = rows;
     P.nsplit = (int32_t)((pr.n + rows - 1) / rows);
     P.hot = hot_share(pr, bytes);
@@ -829,9 +846,9 @@ hmc_status batch_gradient(const BatchLayout& BL, BatchArgs a, int mode, hipStrea
   a.mode = mode;
   const int grid[3] = {persistent_grid((BL.first[0][BL.nprob] + 255) / 256, BL.grid),
                        persistent_grid(BL.first[1][BL.nprob], BL.grid),
-                       persistent_grid(xcd_span(BL.first[2][BL.nprob], kGradChunk), BL.grid)};
+                       persistent_grid(xcd_span(BL.first[2][BL.nprob], grad_chunk(BL.gwaves)), BL.grid)};
   HMC_TRY(timed_launch(s, true, [&] {
-    return hip_status(launch_batch_pass(a, BL.chains, BL.group, BL.lo, grid, pack, s), "batched split-precision pass");
+    return hip_status(launch_batch_pass(a, BL.chains, BL.group, BL.lo, BL.gwaves, grid, pack, s), "batched split-precision pass");
   }));
   return hip_status(launch_batch_epilogue(a, (int)BL.n_epi, s), "batched epilogue");
 }

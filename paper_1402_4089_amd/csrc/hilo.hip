@@ -451,7 +451,7 @@ __device__ __forceinline__ void logits_rows(const Job& j, int64_t rb, double (&l
   softmax_residuals<NB, GROUP>(j, rb, acc, ylab, lacc);
 }
 
-// Gradient partial X^T R of the kGradCols columns from c0 over rows [rbeg, rend) (rbeg a
+// Gradient partial X^T R of the 32 NW columns from c0 over rows [rbeg, rend) (rbeg a
 // multiple of 32), written to gp: element (column j, class kk of group q) at
 // gp[q cstride + j K + kk].
 //
@@ -471,26 +471,25 @@ __device__ __forceinline__ void logits_rows(const Job& j, int64_t rb, double (&l
 // the time that streaming a stage takes. The 16-byte chunks of a staged row are XOR-swizzled
 // by 2 (row % 4 + 4 ((row / 8) % 2)), so that the eight rows a read touches at once fall in
 // different banks. Rows outside the slice and columns past p load as zero.
-constexpr int kGradThreads = 64 * kGradWaves;
-constexpr int kGradPlane = 32 * kGradCols;          // u16 of one plane per stage
-template <int NB, bool LO> constexpr int grad_stage_elems() { return (LO ? 2 : 1) * kGradPlane + NB * 1024; }
+constexpr int grad_plane(int nw) { return 32 * grad_cols(nw); }   // u16 of one plane per stage
+template <int NB, bool LO, int NW> constexpr int grad_stage_elems() { return (LO ? 2 : 1) * grad_plane(NW) + NB * 1024; }
 // residual u16 per thread and piece: the stage's NB * 1024 over the threads, 16 bytes at most
 template <int N_> struct RPieceOf;
 template <> struct RPieceOf<2> { typedef uint32_t type; static constexpr int N = 2; };
 template <> struct RPieceOf<4> { typedef uint2 type; static constexpr int N = 4; };
 template <> struct RPieceOf<8> { typedef u32x4 type; static constexpr int N = 8; };
-template <int NB> struct RPiece : RPieceOf<(NB * 1024 / kGradThreads < 8 ? NB * 1024 / kGradThreads : 8)> {};
+template <int NB, int NW> struct RPiece : RPieceOf<(NB * 16 / NW < 8 ? NB * 16 / NW : 8)> {};
 
-template <int NB, int GROUP, bool LO, int AUX>
-__device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg, int64_t rend,
+template <int NB, int GROUP, bool LO, int AUX, int NW>
+__device__ __forceinline__ void grad_block(const Job& j, int64_t c0, int64_t rbeg, int64_t rend,
                                           float* __restrict__ gp, int64_t cstride,
                                           u16* __restrict__ xs) {
-  constexpr int PL = LO ? 2 : 1;
-  constexpr int XST = PL * kGradPlane;                  // u16 of X per stage
-  constexpr int ST = grad_stage_elems<NB, LO>();
-  constexpr int RN = RPiece<NB>::N;               // residual u16 per thread per piece
-  constexpr int RP = NB * 1024 / (kGradThreads * RN);      // residual pieces per thread per stage
-  typedef typename RPiece<NB>::type rtype;
+  constexpr int PL = LO ? 2 : 1, GC = grad_cols(NW), TH = 64 * NW, GP = grad_plane(NW);
+  constexpr int XST = PL * GP;                  // u16 of X per stage
+  constexpr int ST = grad_stage_elems<NB, LO, NW>();
+  constexpr int RN = RPiece<NB, NW>::N;               // residual u16 per thread per piece
+  constexpr int RP = NB * 1024 / (TH * RN);      // residual pieces per thread per stage
+  typedef typename RPiece<NB, NW>::type rtype;
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int m = lane & 15, g = lane >> 4;
@@ -498,8 +497,8 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
   const int64_t nst = rend > rbeg ? (rend - rbeg + 31) / 32 : 0;
 
   // staging: thread t moves 16-byte chunk sc of rows sr and sr + 16 of each plane, and
-  // residual pieces t, t + kGradThreads, ...
-  const int sr = threadIdx.x / (kGradCols / 8), sc = threadIdx.x % (kGradCols / 8);
+  // residual pieces t, t + TH, ...
+  const int sr = threadIdx.x / (GC / 8), sc = threadIdx.x % (GC / 8);
   const int64_t col = c0 + 8 * sc;
   struct Regs { u32x4 x[2][PL]; rtype r[RP]; };
   // Branch-free buffer loads: the X resource of a stage starts at its first row and ends
@@ -509,7 +508,7 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
   const uint64_t rpk_bytes = (uint64_t)((j.n + kHiloRows - 1) / kHiloRows) * (kHiloRows / 32) * NB * 2048;
   const __amdgpu_buffer_rsrc_t rres = make_rsrc(j.Rpk, rpk_bytes);
   // a chunk at or past column p (the last column block of a problem whose p is not a
-  // multiple of kGradCols) would fetch the row's padding or the next row's bytes for columns that
+  // multiple of 32 NW) would fetch the row's padding or the next row's bytes for columns that
   // are never written: its offset is put out of the resource's range, so it reads zero and
   // moves nothing
   uint32_t xo[2];
@@ -531,7 +530,7 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
     const uint32_t roff = (uint32_t)((real ? row0 / 32 : (int64_t)(rpk_bytes / (NB * 2048))) * NB * 2048);
 #pragma unroll
     for (int i = 0; i < RP; ++i) {
-      const int off = (int)(roff + (i * kGradThreads + threadIdx.x) * RN * 2);
+      const int off = (int)(roff + (i * TH + threadIdx.x) * RN * 2);
       if constexpr (RN == 2)
         R.r[i] = (rtype)__builtin_amdgcn_raw_buffer_load_b32(rres, off, 0, 0);
       else if constexpr (RN == 8)
@@ -540,18 +539,23 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
         R.r[i] = __builtin_bit_cast(rtype, __builtin_amdgcn_raw_buffer_load_b64(rres, off, 0, 0));
     }
   };
+  // XOR of a row's 16-byte chunk index (the same for rows q and q + 4); two 64-column rows share
+  // the 256 bytes that a pair of chunks is spread over
+  auto swizzle = [](int q) {
+    return NW == 2 ? 2 * (((q >> 1) & 1) | ((q >> 2) & 2)) : 2 * ((q & 3) | ((q >> 1) & 4));
+  };
   auto stash = [&](const Regs& R, u16* buf) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int q = sr + 16 * h;
-      const int pos = sc ^ (2 * ((q & 3) | ((q >> 1) & 4)));
+      const int pos = sc ^ swizzle(q);
 #pragma unroll
       for (int pl = 0; pl < PL; ++pl)
-        *reinterpret_cast<u32x4*>(buf + pl * kGradPlane + q * kGradCols + 8 * pos) = R.x[h][pl];
+        *reinterpret_cast<u32x4*>(buf + pl * GP + q * GC + 8 * pos) = R.x[h][pl];
     }
 #pragma unroll
     for (int i = 0; i < RP; ++i)
-      *reinterpret_cast<rtype*>(buf + XST + (i * kGradThreads + threadIdx.x) * RN) = R.r[i];
+      *reinterpret_cast<rtype*>(buf + XST + (i * TH + threadIdx.x) * RN) = R.r[i];
   };
 
   f32x4 acc[2][NB];
@@ -566,7 +570,7 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
   int tcol[2];
 #pragma unroll
   for (int mb = 0; mb < 2; ++mb)
-    tcol[mb] = 8 * ((4 * w + 2 * mb + ((m >> 1) & 1)) ^ (2 * ((m >> 2) | (4 * (g & 1))))) + 4 * (m & 1);
+    tcol[mb] = 8 * ((4 * w + 2 * mb + ((m >> 1) & 1)) ^ swizzle(trow)) + 4 * (m & 1);
   auto compute = [&](const u16* cur) {
     bf16x8 bh[NB], bl[NB];
 #pragma unroll
@@ -579,8 +583,8 @@ __device__ __forceinline__ void grad_cols(const Job& j, int64_t c0, int64_t rbeg
       bf16x8 af[PL];
 #pragma unroll
       for (int pl = 0; pl < PL; ++pl) {
-        const u16* t = cur + pl * kGradPlane + trow * kGradCols + tcol[mb];
-        af[pl] = as_frag(tr_pair(t, t + 4 * kGradCols));
+        const u16* t = cur + pl * GP + trow * GC + tcol[mb];
+        af[pl] = as_frag(tr_pair(t, t + 4 * GC));
       }
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
@@ -670,19 +674,19 @@ __global__ __launch_bounds__(kHiloWaves * 64) void hilo_logits(HiloArgs a) {
   }
 }
 
-// One workgroup per (kGradCols-column block, row slice) item, items slice-major (the column
+// One workgroup per (256-column block, row slice) item, items slice-major (the column
 // blocks of a slice consecutive) in the XCD-aware order; the launch has xcd_span(items,
 // gcols) workgroups.
 template <int NB, bool LO>
-__global__ __launch_bounds__(kGradThreads, 2) void hilo_grad(HiloArgs a, int gcols) {
-  __shared__ __attribute__((aligned(16))) u16 xs[2 * grad_stage_elems<NB, LO>()];
+__global__ __launch_bounds__(512, 2) void hilo_grad(HiloArgs a, int gcols) {
+  __shared__ __attribute__((aligned(16))) u16 xs[2 * grad_stage_elems<NB, LO, 8>()];
   const int64_t it = xcd_item(blockIdx.x, gcols);
   if (it >= (int64_t)gcols * a.nsplit) return;
   const int64_t cb = it % gcols, sl = it / gcols;
   const int64_t rbeg = sl * a.rows_per_split;
   const int64_t rend = rbeg + a.rows_per_split < a.n ? rbeg + a.rows_per_split : a.n;
-  if (hot_slice(sl, a.hot)) grad_cols<NB, NB, LO, kKeep>(job_of(a), cb * kGradCols, rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
-  else grad_cols<NB, NB, LO, kStream>(job_of(a), cb * kGradCols, rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
+  if (hot_slice(sl, a.hot)) grad_block<NB, NB, LO, kKeep, 8>(job_of(a), cb * grad_cols(8), rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
+  else grad_block<NB, NB, LO, kStream, 8>(job_of(a), cb * grad_cols(8), rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -757,13 +761,13 @@ __global__ __launch_bounds__(kHiloWaves * 64, 2) void batch_logits(BatchArgs a) 
   }
 }
 
-template <int NB, int GROUP, bool LO>
-__global__ __launch_bounds__(kGradThreads, 2) void batch_grad(BatchArgs a) {
-  __shared__ __attribute__((aligned(16))) u16 xs[2 * grad_stage_elems<NB, LO>()];
+template <int NB, int GROUP, bool LO, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void batch_grad(BatchArgs a) {
+  __shared__ __attribute__((aligned(16))) u16 xs[2 * grad_stage_elems<NB, LO, NW>()];
   const int64_t total = a.first_grad[a.nprob];
-  const int64_t span = xcd_span(total, kGradChunk);
+  const int64_t span = xcd_span(total, grad_chunk(NW));
   for (int64_t pos = blockIdx.x; pos < span; pos += gridDim.x) {
-    const int64_t it = xcd_item(pos, kGradChunk);
+    const int64_t it = xcd_item(pos, grad_chunk(NW));
     if (it >= total) continue;
     const int b = find_problem(a.first_grad, a.nprob, it);
     const BatchProb& P = a.probs[uniform(b)];
@@ -772,8 +776,8 @@ __global__ __launch_bounds__(kGradThreads, 2) void batch_grad(BatchArgs a) {
     const Job j = job_of(P, nullptr);
     const int64_t rbeg = s * rps, rend = rbeg + rps < j.n ? rbeg + rps : j.n;
     float* gp = uniform(P.gpart + s * P.gstride);
-    if (hot_slice(uniform(P.slice0) + s, uniform(P.hot))) grad_cols<NB, GROUP, LO, kKeep>(j, cb * kGradCols, rbeg, rend, gp, uniform(P.cstride), xs);
-    else grad_cols<NB, GROUP, LO, kStream>(j, cb * kGradCols, rbeg, rend, gp, uniform(P.cstride), xs);
+    if (hot_slice(uniform(P.slice0) + s, uniform(P.hot))) grad_block<NB, GROUP, LO, kKeep, NW>(j, cb * grad_cols(NW), rbeg, rend, gp, uniform(P.cstride), xs);
+    else grad_block<NB, GROUP, LO, kStream, NW>(j, cb * grad_cols(NW), rbeg, rend, gp, uniform(P.cstride), xs);
   }
 }
 
@@ -794,43 +798,48 @@ template hipError_t launch_split<float>(const float*, int64_t, int64_t, int64_t,
 template hipError_t launch_split<double>(const double*, int64_t, int64_t, int64_t, uint16_t*, uint16_t*, int64_t, hipStream_t);
 
 template <int NB, int GROUP, bool LO>
-static hipError_t launch_batch_t(const BatchArgs& a, const int grid[3], bool pack, hipStream_t s) {
+static hipError_t launch_batch_t(const BatchArgs& a, int grad_waves, const int grid[3], bool pack, hipStream_t s) {
   if (pack) hipLaunchKernelGGL((batch_pack<NB, GROUP>), dim3(grid[0]), dim3(256), 0, s, a);
   hipLaunchKernelGGL((batch_logits<NB, GROUP, LO>), dim3(grid[1]), dim3(kHiloWaves * 64), 0, s, a);
-  hipLaunchKernelGGL((batch_grad<NB, GROUP, LO>), dim3(grid[2]), dim3(kGradThreads), 0, s, a);
+  switch (grad_waves) {
+    case 8: hipLaunchKernelGGL((batch_grad<NB, GROUP, LO, 8>), dim3(grid[2]), dim3(512), 0, s, a); break;
+    case 4: hipLaunchKernelGGL((batch_grad<NB, GROUP, LO, 4>), dim3(grid[2]), dim3(256), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((batch_grad<NB, GROUP, LO, 2>), dim3(grid[2]), dim3(128), 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
 // chains x group class blocks (group = 16-class blocks per chain), at most 4 in all
-hipError_t launch_batch_pass(const BatchArgs& a, int chains, int group, bool lo, const int grid[3], bool pack, hipStream_t s) {
+hipError_t launch_batch_pass(const BatchArgs& a, int chains, int group, bool lo, int grad_waves, const int grid[3], bool pack, hipStream_t s) {
 #define HMC_BATCH(C_, G_)                                                                 \
   if (chains == C_ && group == G_)                                                        \
-    return lo ? launch_batch_t<C_ * G_, G_, true>(a, grid, pack, s)                      \
-              : launch_batch_t<C_ * G_, G_, false>(a, grid, pack, s);
+    return lo ? launch_batch_t<C_ * G_, G_, true>(a, grad_waves, grid, pack, s)                      \
+              : launch_batch_t<C_ * G_, G_, false>(a, grad_waves, grid, pack, s);
   HMC_BATCH(1, 1) HMC_BATCH(2, 1) HMC_BATCH(4, 1) HMC_BATCH(1, 2) HMC_BATCH(2, 2) HMC_BATCH(1, 4)
 #undef HMC_BATCH
   return hipErrorInvalidValue;
 }
 
 template <int NB, bool LO>
-static hipError_t launch_hilo_t(const HiloArgs& a, int logits_wg, int grad_cols, bool pack, hipStream_t s) {
+static hipError_t launch_hilo_t(const HiloArgs& a, int logits_wg, int gcols, bool pack, hipStream_t s) {
   const int nks = (a.p + 31) / 32;
   const int packs = (nks * NB * 64 + 255) / 256;
   if (pack) hipLaunchKernelGGL(pack_b_kernel<NB>, dim3(packs), dim3(256), 0, s, a);
   hipLaunchKernelGGL((hilo_logits<NB, LO>), dim3(logits_wg), dim3(kHiloWaves * 64), 0, s, a);
-  const int64_t span = xcd_span((int64_t)grad_cols * a.nsplit, grad_cols);
-  hipLaunchKernelGGL((hilo_grad<NB, LO>), dim3((unsigned)span), dim3(kGradThreads), 0, s, a, grad_cols);
+  const int64_t span = xcd_span((int64_t)gcols * a.nsplit, gcols);
+  hipLaunchKernelGGL((hilo_grad<NB, LO>), dim3((unsigned)span), dim3(512), 0, s, a, gcols);
   return hipGetLastError();
 }
 
-hipError_t launch_hilo(const HiloArgs& a, int nb, bool lo, int logits_wg, int grad_cols, bool pack, hipStream_t s) {
+hipError_t launch_hilo(const HiloArgs& a, int nb, bool lo, int logits_wg, int gcols, bool pack, hipStream_t s) {
   switch (nb * 2 + (lo ? 1 : 0)) {
-    case 2: return launch_hilo_t<1, false>(a, logits_wg, grad_cols, pack, s);
-    case 3: return launch_hilo_t<1, true>(a, logits_wg, grad_cols, pack, s);
-    case 4: return launch_hilo_t<2, false>(a, logits_wg, grad_cols, pack, s);
-    case 5: return launch_hilo_t<2, true>(a, logits_wg, grad_cols, pack, s);
-    case 8: return launch_hilo_t<4, false>(a, logits_wg, grad_cols, pack, s);
-    case 9: return launch_hilo_t<4, true>(a, logits_wg, grad_cols, pack, s);
+    case 2: return launch_hilo_t<1, false>(a, logits_wg, gcols, pack, s);
+    case 3: return launch_hilo_t<1, true>(a, logits_wg, gcols, pack, s);
+    case 4: return launch_hilo_t<2, false>(a, logits_wg, gcols, pack, s);
+    case 5: return launch_hilo_t<2, true>(a, logits_wg, gcols, pack, s);
+    case 8: return launch_hilo_t<4, false>(a, logits_wg, gcols, pack, s);
+    case 9: return launch_hilo_t<4, true>(a, logits_wg, gcols, pack, s);
   }
   return hipErrorInvalidValue;
 }

@@ -124,12 +124,12 @@ constexpr int kHiloRows = kHiloWaves * 16 * kHiloMB;   // rows per logits row bl
 
 // XCD-aware order of the split-precision gradient items (hilo.hip): the launch order is
 // split into chunks of G consecutive items dealt round-robin to the kXcds XCDs; the launch
-// covers xcd_span(items, G) positions. kGradChunk is G for the batched kernel (the column
+// covers xcd_span(items, G) positions. grad_chunk is G for the batched kernel (the column
 // blocks of one row slice of a problem with p <= 2048).
 constexpr int kXcds = 8;
-constexpr int kGradWaves = 8;      // waves of a gradient workgroup, 32 columns each
-constexpr int kGradCols = 32 * kGradWaves;
-constexpr int kGradChunk = 2048 / kGradCols;
+// A gradient workgroup has 8, 4 or 2 waves of 32 columns each.
+constexpr int grad_cols(int waves) { return 32 * waves; }
+constexpr int grad_chunk(int waves) { return 2048 / grad_cols(waves); }
 constexpr int64_t xcd_span(int64_t total, int G) {
   return (total + (int64_t)kXcds * G - 1) / ((int64_t)kXcds * G) * kXcds * G;
 }
@@ -270,7 +270,7 @@ template <typename Tin>
 hipError_t launch_split(const Tin* X, int64_t ldx, int64_t n, int64_t p, uint16_t* hi, uint16_t* lo,
                         int64_t ldo, hipStream_t s);
 
-hipError_t launch_batch_pass(const BatchArgs& a, int chains, int group, bool lo, const int grid[3], bool pack, hipStream_t s);
+hipError_t launch_batch_pass(const BatchArgs& a, int chains, int group, bool lo, int grad_waves, const int grid[3], bool pack, hipStream_t s);
 // grid: {start/accept, epilogue} workgroup counts
 hipError_t launch_batch_start(const BatchArgs& a, int grid, hipStream_t s);
 hipError_t launch_batch_epilogue(const BatchArgs& a, int grid, hipStream_t s);

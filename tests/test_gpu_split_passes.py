@@ -57,9 +57,11 @@ def test_x_beyond_the_memory_side_cache(lib, hi_only, n):
     _check(lib, n, 1000, 10, hi_only, 1024, reps=3)
 
 
+@pytest.mark.parametrize("many", [1, 30, 70])
 @pytest.mark.parametrize("chains,K", [(4, 16), (2, 16), (2, 32), (1, 64), (1, 20), (1, 5)])
-def test_batched_rows_off_cache_lines(lib, chains, K):
-    """Every chain of a batch equals the same problem alone to the form's bar, rows off lines."""
+def test_batched_rows_off_cache_lines(lib, chains, K, many):
+    """Every chain of a batch equals the oracle's gradient to the form's bar, rows off lines; the
+    batch repeated until its gradient workgroups take 64, 128 and 256 columns."""
     import torch
     rng = np.random.default_rng([chains, K])
     probs, Bs, want = [], [], []
@@ -77,10 +79,11 @@ def test_batched_rows_off_cache_lines(lib, chains, K):
         B64 = B.astype(np.float64)
         B64[:, :, -1] = 0.0
         want.append([oracle.log_kernel_and_grad(Xe, y, b) for b in B64])
-    batch = lib.Batch(probs, chains=chains)
+    batch = lib.Batch(probs[:1] * many + probs[1:], chains=chains)
     _, G, logk = batch.zeros_state()
-    batch.logpost_grad(Bs, G, logk)
+    batch.logpost_grad(Bs[:1] * many + Bs[1:], G, logk)
     torch.cuda.synchronize()
+    G, logk = G[many - 1:], logk[many - 1:]
     for b, per in enumerate(want):
         for c, (lk, Go) in enumerate(per):
             g = G[b][c].double().cpu().numpy()
