@@ -163,7 +163,7 @@ def _need(t, name: str, dtype, shape, device):
         raise ValueError(f"{name} is on {t.device}, the problem on {device}")
     if t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:                     # a torch.Size is a tuple
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
@@ -178,9 +178,13 @@ def _need_logk(t, device, count: int = 1):
 
 
 def _stream(stream) -> int | None:
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is not None:       # the handle alone: no Stream object is made (2.7 -> 0.5 us)
+        return raw(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 # ---------------------------------------------------------------- C entry points
