@@ -53,6 +53,8 @@ struct Layout {
   int64_t gstride;      // elements between per-workgroup partial gradients
   bool wide;            // p beyond the row tile: chunked logits + column-owner gradient
   bool tiny;            // small problem: everything in one workgroup
+  bool column;          // one free coefficient column: the one-column pass in place of the row tile
+  bool last_sum;        // the epilogue's last workgroup can sum log K
   int nchunk, tiles_y, nsoft, ngrad, wsplit;
   int64_t wtps;         // wide gradient: 16-row tiles per row slice
   bool hilo, lo;        // bf16 split-precision form (lo: the low plane is present)
@@ -61,7 +63,7 @@ struct Layout {
   size_t off_bpk, off_rpk;
   int nl, np;           // log-likelihood / prior (and kinetic) partial counts
   size_t off_zpart, off_R;
-  size_t off_gpart, off_lpart, off_ppart, off_k0, off_k1, off_eta, off_bp, off_gp, off_scal, off_ctr, total;
+  size_t off_gpart, off_lpart, off_ppart, off_k0, off_k1, off_eta, off_bp, off_gp, off_scal, off_ctr, off_ticket, total;
 };
 
 int class_blocks(int K) { return K <= 16 ? 1 : K <= 32 ? 2 : 4; }
@@ -199,6 +201,8 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
     L->nwg = (int)((L->ntiles + per - 1) / per);
   }
   if ((int64_t)L->nwg > L->ntiles) L->nwg = (int)L->ntiles;
+  L->column = !L->wide && !L->hilo && tu.path == 0 && column_fits(pr->n, pr->p, pr->K, pr->pin_last_class != 0, L->f64);
+  if (L->column) L->nwg = column_workgroups(pr->n);
   const int64_t pk = pr->p * (int64_t)pr->K;
   L->nepi = (int)((pk + kEpiElems - 1) / kEpiElems);
   L->nupd = (int)((pk + kUpdThreads - 1) / kUpdThreads);
@@ -306,6 +310,9 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
   L->off_gp = off;    off = align_up(off + (size_t)pk * L->ts);
   L->off_scal = off;  off = align_up(off + 8 * sizeof(double));
   L->off_ctr = off;   off = align_up(off + 2 * sizeof(int64_t));
+  L->off_ticket = off; off = align_up(off + sizeof(uint32_t));
+  // more partials than one epilogue workgroup per element takes, and few workgroups to count
+  L->last_sum = L->column && L->nwg > kEpiFewMax && L->nepi <= 64;
   L->total = off;
   return HMC_OK;
 }
@@ -444,9 +451,11 @@ hmc_status timed_launch(hipStream_t s, bool idempotent, F&& launch, int passes =
 // One gradient evaluation at Bpos: fused pass, then the epilogue in `mode`.
 // pack: the split-precision pass first packs Bpos into its B operand; a pass that follows a
 // mode-1 epilogue of the same form finds it packed already (that epilogue wrote it).
+// logpost: where log K goes if the layout's epilogue sums it (last_sum).
 template <typename T>
 hmc_status gradient_step(const hmc_problem* pr, const Layout& L, const void* Bpos, void* G,
-                         void* eta, int mode, double eps, void* ws, hipStream_t s, bool pack = true) {
+                         void* eta, int mode, double eps, void* ws, hipStream_t s, bool pack = true,
+                         double* logpost = nullptr) {
   if (L.hilo) {
     HiloArgs h{};
     h.Xhi = static_cast<const uint16_t*>(pr->X);
@@ -505,8 +514,10 @@ hmc_status gradient_step(const hmc_problem* pr, const Layout& L, const void* Bpo
   f.gpart = at<void>(ws, L.off_gpart);
   f.gstride = L.gstride;
   f.lpart = at<double>(ws, L.off_lpart);
+  f.ticket = L.last_sum ? at<uint32_t>(ws, L.off_ticket) : nullptr;
   HMC_TRY(timed_launch(s, true, [&] {
-    return hip_status(launch_fused<T>(f, L.nwg, L.waves, L.mb, L.nb, L.lds, s), "fused pass");
+    return hip_status(L.column ? launch_column<T>(f, L.nwg, s)
+                               : launch_fused<T>(f, L.nwg, L.waves, L.mb, L.nb, L.lds, s), "fused pass");
   }));
   EpiArgs e{};
   e.gpart = f.gpart; e.gstride = L.gstride; e.nwg = L.nwg; e.p = (int32_t)pr->p; e.K = pr->K;
@@ -515,6 +526,9 @@ hmc_status gradient_step(const hmc_problem* pr, const Layout& L, const void* Bpo
   e.h = 0.5 * eps; e.eps = eps; e.mode = mode;
   e.ppart = at<double>(ws, L.off_ppart);
   e.kpart = at<double>(ws, L.off_k1);
+  if (L.last_sum && logpost) {
+    e.ticket = f.ticket; e.lpart = f.lpart; e.nl = L.nl; e.logpost = logpost;
+  }
   return hip_status(launch_epilogue<T>(e, L.nepi, s), "gradient epilogue");
 }
 
@@ -535,7 +549,8 @@ hmc_status do_logpost_grad(const hmc_problem* pr, const Layout& L, const void* B
     const TinyArgs a = tiny_args(pr, const_cast<void*>(B), G, logpost, 0.0, 1, 0);
     return timed_launch(s, true, [&] { return hip_status(launch_tiny<T>(a, s), "one-workgroup gradient"); });
   }
-  HMC_TRY(gradient_step<T>(pr, L, B, G, nullptr, 0, 0.0, ws, s));
+  HMC_TRY(gradient_step<T>(pr, L, B, G, nullptr, 0, 0.0, ws, s, true, logpost));
+  if (L.last_sum) return HMC_OK;
   FinalArgs fa{at<double>(ws, L.off_lpart), L.nl, at<double>(ws, L.off_ppart), L.np, logpost};
   return hip_status(launch_final(fa, s), "log-posterior final sum");
 }
@@ -553,7 +568,9 @@ hmc_status do_leapfrog(const hmc_problem* pr, const Layout& L, void* B, void* et
   sa.B = B; sa.G = G; sa.Bp = B; sa.eta = eta; sa.h = 0.5 * eps; sa.eps = eps; sa.draw = 0;
   HMC_TRY(hip_status(launch_start<T>(sa, L.nupd, s), "leapfrog start"));
   for (int st = 1; st <= L_steps; ++st)
-    HMC_TRY(gradient_step<T>(pr, L, B, G, eta, st < L_steps ? 1 : 2, eps, ws, s, st == 1));
+    HMC_TRY(gradient_step<T>(pr, L, B, G, eta, st < L_steps ? 1 : 2, eps, ws, s, st == 1,
+                             st < L_steps ? nullptr : logpost));
+  if (L.last_sum) return HMC_OK;
   FinalArgs fa{at<double>(ws, L.off_lpart), L.nl, at<double>(ws, L.off_ppart), L.np, logpost};
   return hip_status(launch_final(fa, s), "log-posterior final sum");
 }

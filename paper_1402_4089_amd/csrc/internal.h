@@ -10,6 +10,9 @@ constexpr int kTileRows = 16;      // rows of X per tile: the M dimension of a 1
 constexpr int kMaxFusedWG = 256;   // one workgroup per MI355X compute unit
 constexpr int kEpiElems = 64;      // gradient elements per epilogue workgroup
 constexpr int kUpdThreads = 256;   // elements per refresh / accept workgroup
+// Partial counts up to which the one-thread-per-element epilogue runs (more partials keep the
+// main kernel, whose threads load across partials in parallel).
+constexpr int kEpiFewMax = 64;
 
 // Arguments of the fused log-posterior + gradient pass over X.
 struct FusedArgs {
@@ -25,6 +28,7 @@ struct FusedArgs {
   double* lpart;        // [gridDim.x]: per-workgroup partial log-likelihood
   int32_t link;         // hmc_link: 0 multinomial logit, 1 Poisson (K = 1)
   int32_t pin;          // 1: column K-1 of B is read as zero (its logit is the constant 0)
+  uint32_t* ticket;     // one-column pass: the epilogue's counter, zeroed here, or null
 };
 
 // Arguments of the gradient epilogue (partial reduction, prior, mask, leapfrog kicks).
@@ -46,6 +50,11 @@ struct EpiArgs {
   uint16_t* bpk;        // mode 1, float state: packed split-precision B operand the drifted
                         // position is written into (for the next pass), or null
   int32_t pack_nb;      // its 16-class blocks
+  // the workgroup that takes the last of the counter's gridDim.x tickets sums log K from the
+  // partials (the counter is zero before the launch), or null: a launch of its own does
+  uint32_t* ticket;
+  const double* lpart; int32_t nl;
+  double* logpost;
 };
 
 // Start of a trajectory: optional momentum draw, then the opening half kick and drift.
@@ -248,6 +257,10 @@ struct FinalArgs {
 template <typename T>
 hipError_t launch_fused(const FusedArgs& a, int nwg, int waves, int mb, int nb, size_t lds,
                         hipStream_t s);
+// One-column pass: does it take the problem, and with how many workgroups (partials)?
+bool column_fits(int64_t n, int64_t p, int K, bool pin, bool f64);
+int column_workgroups(int64_t n);
+template <typename T> hipError_t launch_column(const FusedArgs& a, int nwg, hipStream_t s);
 template <typename T> hipError_t launch_epilogue(const EpiArgs& a, int nwg, hipStream_t s);
 template <typename T> hipError_t launch_start(const StartArgs& a, int nwg, hipStream_t s);
 template <typename T> hipError_t launch_accept(const AcceptArgs& a, int nwg, hipStream_t s);

@@ -20,6 +20,35 @@ __device__ double block_sum256(double v, double* sh4) {
   return ((sh4[0] + sh4[1]) + sh4[2]) + sh4[3];
 }
 
+// Sum of v[0..n) by one wave in a fixed order: lane l adds v[l], v[l + 64], ... in turn, then
+// the lanes are combined by wave_sum. Loads are issued eight at a time before their adds, so
+// their latencies overlap (one at a time, a few thousand partials took tens of microseconds).
+__device__ double wave_sum_array(const double* v, int n) {
+  double s = 0.0;
+  int i = threadIdx.x & 63;
+  for (; i + 7 * 64 < n; i += 8 * 64) {
+    double q[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) q[u] = v[i + 64 * u];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += q[u];
+  }
+  for (; i < n; i += 64) s += v[i];
+  return wave_sum(s);
+}
+
+// log K from all partials, by the workgroup whose ticket is the last: its own prior partials are
+// released by the ticket, the others' acquired with it. All threads of wave 0 call it, thread 0
+// after its stores of the workgroup's partials.
+__device__ __forceinline__ void last_workgroup_sum(const EpiArgs& a, int np) {
+  uint32_t mine = 0;
+  if (threadIdx.x == 0) mine = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+  if ((uint32_t)__builtin_amdgcn_readfirstlane((int)mine) + 1u != gridDim.x) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  const double v = wave_sum_array(a.lpart, a.nl) + wave_sum_array(a.ppart, np);
+  if (threadIdx.x == 0) *a.logpost = v;
+}
+
 // Prior, mask, the kicks and drift of `mode`, and the packed B operand for one gradient
 // element e (< p K) whose likelihood part, summed over the partials, is gsum; pr and ke gain
 // the element's prior log-density and kinetic energy.
@@ -57,7 +86,10 @@ __device__ __forceinline__ void epi_element(const EpiArgs& a, int64_t e, T bt, T
 // (t % GROUPS) of the partials w = t / GROUPS, + SLICES, ... (every partial stride is a
 // multiple of 64 elements, so the loads are aligned and many are in flight); the slices
 // are then combined in a fixed order and wave 0 applies prior, mask and kicks.
-template <typename T>
+// LAST: the last of its workgroups also sums log K, in place of a launch (p = 1000,
+// FP32, one column: 5.6 us in one kernel against 4.0 + 2.6 in two; with more than 64 workgroups
+// the launch stays, since they would queue at the counter).
+template <typename T, bool LAST>
 __global__ __launch_bounds__(256) void epilogue_kernel(EpiArgs a) {
   constexpr int VEC = 16 / sizeof(T);             // elements per 16-byte load
   constexpr int GROUPS = kEpiElems / VEC;         // 16-byte groups per 64 elements
@@ -121,14 +153,12 @@ __global__ __launch_bounds__(256) void epilogue_kernel(EpiArgs a) {
       a.ppart[blockIdx.x] = pr;
       if (a.mode == 2) a.kpart[blockIdx.x] = ke;
     }
+    if constexpr (LAST) last_workgroup_sum(a, (int)gridDim.x);
   }
 }
 
 // Partial slices the main epilogue sums in parallel (16 for float, 8 for double).
 template <typename T> constexpr int epi_slices() { return 256 * (16 / (int)sizeof(T)) / kEpiElems; }
-// Partial counts up to which the one-thread-per-element epilogue runs (more partials keep the
-// main kernel, whose threads load across partials in parallel).
-constexpr int kEpiFewMax = 64;
 
 // The same epilogue with one thread per gradient element, 256 elements per workgroup (a
 // quarter of the workgroups, every thread busy), for partial counts up to kEpiFewMax. Wave w's
@@ -218,24 +248,6 @@ __global__ __launch_bounds__(256) void start_kernel(StartArgs a) {
   }
 }
 
-// Fixed-order float64 sum of a small device array by one wave.
-// Sum of v[0..n) by one wave in a fixed order: lane l adds v[l], v[l + 64], ... in turn, then
-// the lanes are combined by wave_sum. Loads are issued eight at a time before their adds, so
-// their latencies overlap (one at a time, a few thousand partials took tens of microseconds).
-__device__ double wave_sum_array(const double* v, int n) {
-  double s = 0.0;
-  int i = threadIdx.x & 63;
-  for (; i + 7 * 64 < n; i += 8 * 64) {
-    double q[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) q[u] = v[i + 64 * u];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += q[u];
-  }
-  for (; i < n; i += 64) s += v[i];
-  return wave_sum(s);
-}
-
 template <typename T>
 __global__ __launch_bounds__(256) void accept_kernel(AcceptArgs a) {
   __shared__ int sh_acc;
@@ -299,8 +311,10 @@ template <typename T>
 hipError_t launch_epilogue(const EpiArgs& a, int nwg, hipStream_t s) {
   if (a.nwg <= kEpiFewMax)
     hipLaunchKernelGGL(epilogue_few<T>, dim3((nwg + 3) / 4), dim3(256), 0, s, a);
+  else if (a.ticket)
+    hipLaunchKernelGGL((epilogue_kernel<T, true>), dim3(nwg), dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL(epilogue_kernel<T>, dim3(nwg), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((epilogue_kernel<T, false>), dim3(nwg), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 template <typename T>
