@@ -175,7 +175,7 @@ __global__ __launch_bounds__(NW * 64) void fused_logpost_grad(FusedArgs a) {
   // into another, so it does not wait for the copy in flight before them.
   auto step = [&](auto ml, int64_t tile, T* __restrict__ cur, T* __restrict__ nxt,
                   const int* __restrict__ ycur, int* __restrict__ ynxt, T* __restrict__ zx,
-                  T* __restrict__ rx) {
+                  T* __restrict__ rx) __attribute__((always_inline)) {
     constexpr int ML = decltype(ml)::value;             // column blocks that this wave takes
     __builtin_amdgcn_s_waitcnt(kWaitVm0);               // this wave's copies of `tile` landed
     if (zbits) {
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(NW * 64) void fused_logpost_grad(FusedArgs a) {
         for (int nb = 0; nb < NB; ++nb) gacc[m][nb] = M::run(xa[m][s], rr[nb][s], gacc[m][nb]);
   };
 
-  auto run = [&](auto ml) {
+  auto run = [&](auto ml) __attribute__((always_inline)) {
     int64_t tile = blockIdx.x;
     // Unrolled by two so each buffer is named statically in the code that reads it.
     while (tile < a.ntiles) {
@@ -363,9 +363,11 @@ __global__ __launch_bounds__(NW * 64) void fused_logpost_grad(FusedArgs a) {
   // are zero) and of the gradient. All waves pass the same barriers. The matrix instructions of
   // all NW MB blocks take 1.7 of the 2.7 us per tile, in turn with the softmax, so 14 blocks of
   // 64 less (n = 60000, p = 785, K = 10, FP32) took 7 us from a pass of 45.
+  // (Two variants have no registers to spare for the choice.)
+  constexpr bool SKIP = MB * NB < 16 && !(sizeof(T) == 8 && LINK == 2);
   const int live = ((p + 15) / 16 - w + NW - 1) / NW;
-  if (MB >= 2 && live <= MB / 2) run(std::integral_constant<int, MB >= 2 ? MB / 2 : MB>{});
-  else if (MB >= 4 && live <= MB / 4 * 3) run(std::integral_constant<int, MB >= 4 ? MB / 4 * 3 : MB>{});
+  if (SKIP && MB >= 2 && live <= MB / 2) run(std::integral_constant<int, SKIP && MB >= 2 ? MB / 2 : MB>{});
+  else if (SKIP && MB >= 4 && live <= MB / 4 * 3) run(std::integral_constant<int, SKIP && MB >= 4 ? MB / 4 * 3 : MB>{});
   else run(std::integral_constant<int, MB>{});
 #undef HMC_ISSUE
 
