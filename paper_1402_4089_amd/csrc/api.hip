@@ -52,7 +52,7 @@ struct Layout {
   int nwg, nepi, nupd;
   int64_t gstride;      // elements between per-workgroup partial gradients
   bool wide;            // p beyond the row tile: chunked logits + column-owner gradient
-  bool tiny;            // small problem: everything in one workgroup
+  bool tiny, tiny_grad; // small problem: updates and transitions, or a gradient, in one workgroup
   bool column;          // one free coefficient column: the one-column pass in place of the row tile
   bool last_sum;        // the epilogue's last workgroup can sum log K
   int nchunk, tiles_y, nsoft, ngrad, wsplit;
@@ -169,7 +169,9 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
   if (L->hilo != (tu.path == 3) && tu.path != 0)
     return fail(HMC_ERR_ARG, "tuning.path %d does not fit X format %d (path 3 is the bf16 formats' only path)",
                 tu.path, pr->xfmt);
-  L->tiny = !L->hilo && tu.path == 0 && tiny_fits(pr->n, pr->p, pr->K, pr->pin_last_class != 0, L->f64);
+  const bool small = !L->hilo && tu.path == 0;
+  L->tiny = small && tiny_fits(pr->n, pr->p, pr->K, pr->pin_last_class != 0, L->f64, true);
+  L->tiny_grad = small && tiny_fits(pr->n, pr->p, pr->K, pr->pin_last_class != 0, L->f64, false);
   if (tu.path == 1 || tu.path == 0) {
     const bool ruled = tu.waves == 0 && tu.mb == 0;
     bool ok;
@@ -545,7 +547,7 @@ TinyArgs tiny_args(const hmc_problem* pr, void* B, void* G, double* logpost, dou
 template <typename T>
 hmc_status do_logpost_grad(const hmc_problem* pr, const Layout& L, const void* B, double* logpost,
                            void* G, void* ws, hipStream_t s) {
-  if (L.tiny) {
+  if (L.tiny_grad) {
     const TinyArgs a = tiny_args(pr, const_cast<void*>(B), G, logpost, 0.0, 1, 0);
     return timed_launch(s, true, [&] { return hip_status(launch_tiny<T>(a, s), "one-workgroup gradient"); });
   }

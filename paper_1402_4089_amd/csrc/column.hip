@@ -251,10 +251,12 @@ hipError_t launch_one(const FusedArgs& a, int nwg, hipStream_t s) {
 }  // namespace
 
 // One free column, and columns that the lanes of half a wave hold: as many as the row tile takes.
-// A small float64 problem stays with the row tile, whose waves have less to set up (n = 5000,
-// p = 100: 11.8 us against 12.9; n = 2000, p = 500: 13.1 against 12.0).
+// Small problems stay with the row tile, whose waves have less to set up: float32, n = 50, p = 100:
+// 8.4 us against 8.9 (n = 1000: 10.0 against 9.6; n = 50, p = 192: 9.5 against 9.0); float64,
+// n = 5000, p = 100: 11.8 against 12.9.
 bool column_fits(int64_t n, int64_t p, int K, bool pin, bool f64) {
-  return (pin ? K - 1 : K) == 1 && (f64 ? p <= 512 && n * p >= (1 << 20) : p <= 1024);
+  if ((pin ? K - 1 : K) != 1) return false;
+  return f64 ? p <= 512 && n * p >= (1 << 20) : p <= 1024 && (p > 128 || n >= 512);
 }
 // A workgroup per compute unit, each wave with a pair of rows at least.
 int column_workgroups(int64_t n) {

@@ -266,8 +266,8 @@ template <typename T> hipError_t launch_start(const StartArgs& a, int nwg, hipSt
 template <typename T> hipError_t launch_accept(const AcceptArgs& a, int nwg, hipStream_t s);
 hipError_t launch_final(const FinalArgs& a, hipStream_t s);
 
-// Does one workgroup take a problem of these sizes?
-bool tiny_fits(int64_t n, int64_t p, int K, bool pin, bool f64);
+// Does one workgroup take a problem of these sizes, for updates (and transitions) or one gradient?
+bool tiny_fits(int64_t n, int64_t p, int K, bool pin, bool f64, bool update);
 template <typename T> hipError_t launch_tiny(const TinyArgs& a, hipStream_t s);
 
 template <typename T> int wide_chunk_cols();

@@ -7,8 +7,8 @@
 // workgroup barriers: a thread per row of X forms the row's logits, softmax and residuals; a
 // thread per column of X and group of rows sums x r over its rows in float64 for every free
 // class; a thread per element adds the prior and applies the kicks and the drift. LDS reads and
-// the latency of the float64 functions bound it, so it is used while a thread has one row, one
-// element and few terms (tiny_fits). That transition now takes 45 us, 3.7 per update (timed with
+// the latency of the float64 functions bound it, so it is used where its time is below the
+// general path's launches (tiny_fits). That transition now takes 45 us, 3.7 per update (timed with
 // phases left out: logits 1.3, softmax 1.1, gradient 1.4 of 4.9 in a form with a thread per
 // gradient element, whose LDS reads were twice as many), and one gradient 9.6.
 //
@@ -299,10 +299,26 @@ hipError_t launch_one(const TinyArgs& a, size_t lds, hipStream_t s) {
 
 }  // namespace
 
-bool tiny_fits(int64_t n, int64_t p, int K, bool pin, bool f64) {
+// Where one workgroup beats the general path's kernels. Both times are near linear, here in us as
+// measured at 400 sizes (f = padded free classes; p f <= 512 leaves a thread two gradient
+// shares at most, and beyond it both the time and its spread double); the rule asks for 10% less
+// per update and 5% less per gradient. Per update in FP32: p = 64 at n = 100, K = 3: 4.3 against
+// 6.6; p = 128: 7.6 against 6.7, not taken. Per gradient: p = 20 at n = 500, K = 3: 9.4 against
+// 9.2 in a graph and about 13 launched singly; p = 256 at n = 100, K = 1: 21.7 against 9.6, not taken.
+bool tiny_fits(int64_t n, int64_t p, int K, bool pin, bool f64, bool update) {
   if (n > 1024 || p > 256 || K > 16 || p * K > 1024 || n * p * K > (int64_t)1 << 16) return false;
-  const int th = tiny_threads(n, p * K);
-  return tiny_layout((int)n, (int)p, class_pad(pin ? K - 1 : K), th, f64 ? 8 : 4).total <= kTinyLds;
+  const int fp = class_pad(pin ? K - 1 : K);
+  if (p * fp > 512) return false;
+  const double N = (double)n, P = (double)p, F = fp, far = p > 128 ? 1.2 : 0.0;   // far: a wider row tile
+  const double here =
+      update ? (f64 ? 1.7 + P * (0.024 + 0.0116 * F) + N * (0.0010 + 0.00125 * F)
+                    : 1.3 + P * (0.030 + 0.0078 * F) + N * (0.0016 + 0.00063 * F))
+             : (f64 ? 5.4 + P * (0.034 + 0.0133 * F) + N * (0.0037 + 0.00122 * F)
+                    : 5.0 + P * (0.035 + 0.0100 * F) + N * (0.0042 + 0.00061 * F));
+  const double general = update ? (f64 ? 6.4 + 0.0046 * N : 6.1 + 0.0023 * N) + far
+                                : (f64 ? 8.4 + 0.0044 * N : 8.3 + 0.0022 * N) + far;
+  if (here * (update ? 1.10 : 1.05) > general) return false;
+  return tiny_layout((int)n, (int)p, fp, tiny_threads(n, p * K), f64 ? 8 : 4).total <= kTinyLds;
 }
 
 template <typename T>
