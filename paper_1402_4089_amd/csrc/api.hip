@@ -58,7 +58,7 @@ struct Layout {
   int nchunk, tiles_y, nsoft, ngrad, wsplit;
   int64_t wtps;         // wide gradient: 16-row tiles per row slice
   bool hilo, lo;        // bf16 split-precision form (lo: the low plane is present)
-  int hl_logits_wg, hl_cols, hl_nsplit;
+  int hl_logits_wg, hl_gwaves, hl_nsplit;
   int64_t hl_rps;       // rows per gradient slice
   size_t off_bpk, off_rpk;
   int nl, np;           // log-likelihood / prior (and kinetic) partial counts
@@ -209,17 +209,20 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
   L->nepi = (int)((pk + kEpiElems - 1) / kEpiElems);
   L->nupd = (int)((pk + kUpdThreads - 1) / kUpdThreads);
   const int KP = 16 * L->nb;
-  L->hl_logits_wg = L->hl_cols = L->hl_nsplit = 0;
+  L->hl_logits_wg = L->hl_gwaves = L->hl_nsplit = 0;
   L->hl_rps = 0;
   if (L->hilo) {
-    // logits: row blocks of kHiloRows rows; gradient: 256-column blocks times row
+    // logits: row blocks of kHiloRows rows; gradient: 256-column blocks (fewer waves for few
+    // columns) times row
     // slices, as many slices as give about 2048 items of 128 columns
     const int64_t rows = kHiloRows;
     const int64_t nrb = (pr->n + rows - 1) / rows;
     if (tu.grid > 65536) return fail(HMC_ERR_ARG, "tuning.grid = %d must be <= 65536", tu.grid);
     const int64_t lwg = tu.grid ? tu.grid : 2048;
     L->hl_logits_wg = (int)(nrb < lwg ? nrb : lwg);
-    L->hl_cols = (int)((pr->p + grad_cols(8) - 1) / grad_cols(8));
+    // no wider than the columns there are: ten updates at n = 5000, p = 64, K = 40 (bf16) 157 us
+    // with two waves per item against 165 with eight, at n = 300, p = 100, K = 5 122 against 128
+    L->hl_gwaves = pr->p <= grad_cols(2) ? 2 : pr->p <= grad_cols(4) ? 4 : 8;
     if (tu.rows_per_slice) {
       if (tu.rows_per_slice % 32) return fail(HMC_ERR_ARG, "tuning.rows_per_slice = %d must be a multiple of 32", tu.rows_per_slice);
       L->hl_rps = std::min<int64_t>(tu.rows_per_slice, (pr->n + 31) / 32 * 32);
@@ -470,7 +473,7 @@ hmc_status gradient_step(const hmc_problem* pr, const Layout& L, const void* Bpo
     h.n = pr->n; h.p = (int32_t)pr->p; h.K = pr->K; h.pin = pr->pin_last_class;
     h.hot = hot_share(*pr, plane_bytes(*pr));
     HMC_TRY(timed_launch(s, true, [&] {
-      return hip_status(launch_hilo(h, L.nb, L.lo, L.hl_logits_wg, L.hl_cols, pack, s), "split-precision pass");
+      return hip_status(launch_hilo(h, L.nb, L.lo, L.hl_logits_wg, L.hl_gwaves, pack, s), "split-precision pass");
     }));
     EpiArgs e{};
     e.gpart = h.gpart; e.gstride = L.gstride; e.nwg = L.hl_nsplit; e.p = (int32_t)pr->p; e.K = pr->K;

@@ -674,19 +674,19 @@ __global__ __launch_bounds__(kHiloWaves * 64) void hilo_logits(HiloArgs a) {
   }
 }
 
-// One workgroup per (256-column block, row slice) item, items slice-major (the column
-// blocks of a slice consecutive) in the XCD-aware order; the launch has xcd_span(items,
+// One workgroup of NW waves per (32 NW-column block, row slice) item, items slice-major (the
+// column blocks of a slice consecutive) in the XCD-aware order; the launch has xcd_span(items,
 // gcols) workgroups.
-template <int NB, bool LO>
-__global__ __launch_bounds__(512, 2) void hilo_grad(HiloArgs a, int gcols) {
-  __shared__ __attribute__((aligned(16))) u16 xs[2 * grad_stage_elems<NB, LO, 8>()];
+template <int NB, bool LO, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void hilo_grad(HiloArgs a, int gcols) {
+  __shared__ __attribute__((aligned(16))) u16 xs[2 * grad_stage_elems<NB, LO, NW>()];
   const int64_t it = xcd_item(blockIdx.x, gcols);
   if (it >= (int64_t)gcols * a.nsplit) return;
   const int64_t cb = it % gcols, sl = it / gcols;
   const int64_t rbeg = sl * a.rows_per_split;
   const int64_t rend = rbeg + a.rows_per_split < a.n ? rbeg + a.rows_per_split : a.n;
-  if (hot_slice(sl, a.hot)) grad_block<NB, NB, LO, kKeep, 8>(job_of(a), cb * grad_cols(8), rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
-  else grad_block<NB, NB, LO, kStream, 8>(job_of(a), cb * grad_cols(8), rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
+  if (hot_slice(sl, a.hot)) grad_block<NB, NB, LO, kKeep, NW>(job_of(a), cb * grad_cols(NW), rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
+  else grad_block<NB, NB, LO, kStream, NW>(job_of(a), cb * grad_cols(NW), rbeg, rend, a.gpart + sl * a.gstride, 0, xs);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -822,24 +822,27 @@ hipError_t launch_batch_pass(const BatchArgs& a, int chains, int group, bool lo,
 }
 
 template <int NB, bool LO>
-static hipError_t launch_hilo_t(const HiloArgs& a, int logits_wg, int gcols, bool pack, hipStream_t s) {
+static hipError_t launch_hilo_t(const HiloArgs& a, int logits_wg, int grad_waves, bool pack, hipStream_t s) {
+  const int gcols = (a.p + grad_cols(grad_waves) - 1) / grad_cols(grad_waves);
   const int nks = (a.p + 31) / 32;
   const int packs = (nks * NB * 64 + 255) / 256;
   if (pack) hipLaunchKernelGGL(pack_b_kernel<NB>, dim3(packs), dim3(256), 0, s, a);
   hipLaunchKernelGGL((hilo_logits<NB, LO>), dim3(logits_wg), dim3(kHiloWaves * 64), 0, s, a);
   const int64_t span = xcd_span((int64_t)gcols * a.nsplit, gcols);
-  hipLaunchKernelGGL((hilo_grad<NB, LO>), dim3((unsigned)span), dim3(512), 0, s, a, gcols);
+  if (grad_waves == 2) hipLaunchKernelGGL((hilo_grad<NB, LO, 2>), dim3((unsigned)span), dim3(128), 0, s, a, gcols);
+  else if (grad_waves == 4) hipLaunchKernelGGL((hilo_grad<NB, LO, 4>), dim3((unsigned)span), dim3(256), 0, s, a, gcols);
+  else hipLaunchKernelGGL((hilo_grad<NB, LO, 8>), dim3((unsigned)span), dim3(512), 0, s, a, gcols);
   return hipGetLastError();
 }
 
-hipError_t launch_hilo(const HiloArgs& a, int nb, bool lo, int logits_wg, int gcols, bool pack, hipStream_t s) {
+hipError_t launch_hilo(const HiloArgs& a, int nb, bool lo, int logits_wg, int grad_waves, bool pack, hipStream_t s) {
   switch (nb * 2 + (lo ? 1 : 0)) {
-    case 2: return launch_hilo_t<1, false>(a, logits_wg, gcols, pack, s);
-    case 3: return launch_hilo_t<1, true>(a, logits_wg, gcols, pack, s);
-    case 4: return launch_hilo_t<2, false>(a, logits_wg, gcols, pack, s);
-    case 5: return launch_hilo_t<2, true>(a, logits_wg, gcols, pack, s);
-    case 8: return launch_hilo_t<4, false>(a, logits_wg, gcols, pack, s);
-    case 9: return launch_hilo_t<4, true>(a, logits_wg, gcols, pack, s);
+    case 2: return launch_hilo_t<1, false>(a, logits_wg, grad_waves, pack, s);
+    case 3: return launch_hilo_t<1, true>(a, logits_wg, grad_waves, pack, s);
+    case 4: return launch_hilo_t<2, false>(a, logits_wg, grad_waves, pack, s);
+    case 5: return launch_hilo_t<2, true>(a, logits_wg, grad_waves, pack, s);
+    case 8: return launch_hilo_t<4, false>(a, logits_wg, grad_waves, pack, s);
+    case 9: return launch_hilo_t<4, true>(a, logits_wg, grad_waves, pack, s);
   }
   return hipErrorInvalidValue;
 }

@@ -278,7 +278,7 @@ template <typename T>
 hipError_t launch_wide(const WideArgs& a, int nb, int logits_tiles_y, int softmax_wg, int grad_wg,
                        hipStream_t s);
 
-hipError_t launch_hilo(const HiloArgs& a, int nb, bool lo, int logits_wg, int grad_cols, bool pack, hipStream_t s);
+hipError_t launch_hilo(const HiloArgs& a, int nb, bool lo, int logits_wg, int grad_waves, bool pack, hipStream_t s);
 template <typename Tin>
 hipError_t launch_split(const Tin* X, int64_t ldx, int64_t n, int64_t p, uint16_t* hi, uint16_t* lo,
                         int64_t ldo, hipStream_t s);
