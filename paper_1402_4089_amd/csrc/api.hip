@@ -56,6 +56,7 @@ struct Layout {
   bool column;          // one free coefficient column: the one-column pass in place of the row tile
   bool last_sum;        // the epilogue's last workgroup can sum log K
   int nchunk, tiles_y, nsoft, ngrad, wsplit;
+  bool narrow;          // wide gradient: 16 columns per wave
   int64_t wtps;         // wide gradient: 16-row tiles per row slice
   bool hilo, lo;        // bf16 split-precision form (lo: the low plane is present)
   int hl_logits_wg, hl_gwaves, hl_nsplit;
@@ -256,7 +257,6 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
       L->tiles_y = (int)(L->ntiles < tu.grid ? L->ntiles : tu.grid);
     }
     L->nsoft = (int)(4 * L->ntiles);                 // softmax workgroups of 4 rows, whole tiles
-    L->ngrad = wide_grad_groups(pr->p, L->f64);
     // few column blocks: split the rows too (partials reduced by the shared epilogue)
     L->wsplit = 1;
     L->wtps = 0;
@@ -276,6 +276,14 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
         L->wsplit = (int)((L->ntiles + L->wtps - 1) / L->wtps);
       }
     }
+    // 16 columns per wave while the wider spans would give few workgroups for the compute units;
+    // with four class blocks a wave's chain is longer, so up to more of them (us for five updates,
+    // wide against narrow. FP32: n = 1000, p = 2500, K = 60: 190, 164; n = 5000, p = 4000, K = 50:
+    // 442, 397; n = 10000, p = 5000, K = 20, 260 workgroups: 464, 517; n = 20000, p = 1100, K = 10,
+    // 395: 272, 290. FP64: n = 500, p = 1500, K = 50, 96: 150, 138; n = 8000, p = 700, K = 30, 252:
+    // 220, 229)
+    L->narrow = (int64_t)wide_grad_groups(pr->p, L->f64, false) * L->wsplit <= (L->f64 ? 128 : L->nb == 4 ? 512 : 256);
+    L->ngrad = wide_grad_groups(pr->p, L->f64, L->narrow);
     L->nl = L->nsoft;
     L->np = L->wsplit > 1 ? L->nepi : L->ngrad;
     L->gstride = L->wsplit > 1 ? (pk + 63) / 64 * 64 : 0;
@@ -500,7 +508,7 @@ hmc_status gradient_step(const hmc_problem* pr, const Layout& L, const void* Bpo
     w.gpart = at<void>(ws, L.off_gpart); w.gstride = L.gstride;
     // with one row slice the gradient kernel applies the leapfrog update itself: not idempotent
     HMC_TRY(timed_launch(s, L.wsplit > 1, [&] {
-      return hip_status(launch_wide<T>(w, L.nb, L.tiles_y, L.nsoft, L.ngrad, s), "wide pass");
+      return hip_status(launch_wide<T>(w, L.nb, L.tiles_y, L.nsoft, L.ngrad, L.narrow, s), "wide pass");
     }));
     if (L.wsplit == 1) return HMC_OK;
     EpiArgs e{};

@@ -271,12 +271,12 @@ bool tiny_fits(int64_t n, int64_t p, int K, bool pin, bool f64, bool update);
 template <typename T> hipError_t launch_tiny(const TinyArgs& a, hipStream_t s);
 
 template <typename T> int wide_chunk_cols();
-int wide_grad_groups(int64_t p, bool f64);
+int wide_grad_groups(int64_t p, bool f64, bool narrow);
 int wide_row_slices(int64_t p, int nb, bool f64);
 int wide_logits_resident(int nb);
 template <typename T>
 hipError_t launch_wide(const WideArgs& a, int nb, int logits_tiles_y, int softmax_wg, int grad_wg,
-                       hipStream_t s);
+                       bool narrow, hipStream_t s);
 
 hipError_t launch_hilo(const HiloArgs& a, int nb, bool lo, int logits_wg, int grad_waves, bool pack, hipStream_t s);
 template <typename Tin>

@@ -12,6 +12,8 @@
 //                 for the shared epilogue.
 // X is read twice per gradient, which bounds the path: the matrix cores are busy a third of the
 // time. All loads go through buffer resources whose bounds make rows past n read as zero.
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace hmcx {
@@ -213,6 +215,20 @@ __global__ __launch_bounds__(256) void wide_softmax(WideArgs a) {
   if (lane == 0) a.lpart[blockIdx.x] = l;
 }
 
+// W consecutive elements at a byte offset: one, or those of 16 bytes.
+template <typename T, int W> struct Run { typedef vec16<T> type; };
+template <typename T> struct Run<T, 1> { typedef T type; };
+template <typename T, int W>
+__device__ __forceinline__ typename Run<T, W>::type ld_run(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  if constexpr (W > 1) return ld16<T>(r, off);
+  else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+  else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+}
+template <typename V> __device__ __forceinline__ auto run_elem(const V& v, int e) {
+  if constexpr (std::is_arithmetic_v<V>) return v;
+  else return v[e];
+}
+
 // Column-owner gradient. A wave owns 256 bytes of a row, 16 E consecutive columns. A lane's 16-byte load
 // takes E consecutive columns of one row; as which column of G a row of the MFMA's output means
 // is free, element e of the load is the A operand of a block that holds columns E c + e, c = 0
@@ -223,7 +239,9 @@ __global__ __launch_bounds__(256) void wide_softmax(WideArgs a) {
 // its partial X^T R to gpart for the shared epilogue kernel. Measured against one element per
 // lane: n = 2000, p = 50000, K = 4, FP32 75.5 -> 71.4 us (5.6 TB/s); a whole gradient of
 // n = 5000, p = 1000, K = 10, FP64 46 -> 33 us, n = 2000, p = 10000, K = 4, FP64 84 -> 64 us.
-template <typename T, int NB>
+// W: elements of a load, E, or 1 (16 columns per wave) where the wider spans leave compute units
+// idle and each wave E times the matrix instructions.
+template <typename T, int NB, int W>
 __global__ __launch_bounds__(kWideWaves * 64, (sizeof(T) * NB <= 8 ? 3 : sizeof(T) * NB <= 16 ? 2 : 1)) void wide_grad(WideArgs a) {
   __shared__ double sh4[2][4];
   using M = Mma<T>;
@@ -235,12 +253,12 @@ __global__ __launch_bounds__(kWideWaves * 64, (sizeof(T) * NB <= 8 ? 3 : sizeof(
   const int g = lane >> 4, c = lane & 15;
   const int p = a.p, K = a.K;
   const int64_t n = a.n, ldx = a.ldx;
-  const int j0 = ((int)blockIdx.x * kWideWaves + w) * 16 * E;   // first column of this wave
+  const int j0 = ((int)blockIdx.x * kWideWaves + w) * 16 * W;   // first column of this wave
 
   const uint64_t x_bytes = (uint64_t)((n - 1) * ldx + p) * sizeof(T);
-  acc_t gacc[E][NB];
+  acc_t gacc[W][NB];
 #pragma unroll
-  for (int e = 0; e < E; ++e)
+  for (int e = 0; e < W; ++e)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) gacc[e][nb] = acc_t{0, 0, 0, 0};
   const int64_t ntiles = (n + kTileRows - 1) / kTileRows;
@@ -255,11 +273,11 @@ __global__ __launch_bounds__(kWideWaves * 64, (sizeof(T) * NB <= 8 ? 3 : sizeof(
   // the issue stays free of branches. A lane whose columns lie past p loads from an
   // offset past every resource's end: zeros, no traffic (columns past p only feed columns of
   // G that are not written).
-  struct Regs { vec16<T> xa[U][4], ra[U][NB][RB]; };
-  const bool live = j0 + c * E < p;
+  struct Regs { typename Run<T, W>::type xa[U][4]; vec16<T> ra[U][NB][RB]; };
+  const bool live = j0 + c * W < p;
   uint32_t xoff[4];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) xoff[s] = (uint32_t)(((int64_t)M::row(s, g) * ldx + j0 + c * E) * sizeof(T));
+  for (int s = 0; s < 4; ++s) xoff[s] = (uint32_t)(((int64_t)M::row(s, g) * ldx + j0 + c * W) * sizeof(T));
   const uint32_t xstep = (uint32_t)(kTileRows * ldx * sizeof(T));
   auto load = [&](int64_t k, Regs& rg) {
     const bool real = k >= 0;
@@ -274,7 +292,7 @@ __global__ __launch_bounds__(kWideWaves * 64, (sizeof(T) * NB <= 8 ? 3 : sizeof(
       // the second tile of a slice's odd count belongs to the next slice: not read
       const bool in = t0 + u < tend;
 #pragma unroll
-      for (int s = 0; s < 4; ++s) rg.xa[u][s] = ld16<T>(xr, in && live ? xoff[s] + u * xstep : 0xFFFFFFF0u);
+      for (int s = 0; s < 4; ++s) rg.xa[u][s] = ld_run<T, W>(xr, in && live ? xoff[s] + u * xstep : 0xFFFFFFF0u);
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -288,10 +306,10 @@ __global__ __launch_bounds__(kWideWaves * 64, (sizeof(T) * NB <= 8 ? 3 : sizeof(
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int e = 0; e < E; ++e)
+        for (int e = 0; e < W; ++e)
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb)
-            gacc[e][nb] = M::run(rg.xa[u][s][e], rg.ra[u][nb][s / E][s % E], gacc[e][nb]);
+            gacc[e][nb] = M::run(run_elem(rg.xa[u][s], e), rg.ra[u][nb][s / E][s % E], gacc[e][nb]);
   };
   // Explicit waits leave the group just issued in flight (the compiler, left to itself,
   // waits for every load before the first MFMA of the rotated loop).
@@ -310,8 +328,8 @@ __global__ __launch_bounds__(kWideWaves * 64, (sizeof(T) * NB <= 8 ? 3 : sizeof(
     mma(r1);
   }
 
-  // row r of accumulator e is column j0 + E row + e
-  auto column = [&](int e, int r) { return j0 + M::row(r, g) * E + e; };
+  // row r of accumulator e is column j0 + W row + e
+  auto column = [&](int e, int r) { return j0 + M::row(r, g) * W + e; };
   if (gridDim.y > 1) {
     T* gp = static_cast<T*>(a.gpart) + (int64_t)blockIdx.y * a.gstride;
 #pragma unroll
@@ -319,7 +337,7 @@ __global__ __launch_bounds__(kWideWaves * 64, (sizeof(T) * NB <= 8 ? 3 : sizeof(
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
+        for (int e = 0; e < W; ++e) {
           const int j = column(e, r), k = nb * 16 + c;
           if (j < p && k < K) gp[(int64_t)j * K + k] = gacc[e][nb][r];
         }
@@ -337,7 +355,7 @@ __global__ __launch_bounds__(kWideWaves * 64, (sizeof(T) * NB <= 8 ? 3 : sizeof(
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int el = 0; el < E; ++el) {
+      for (int el = 0; el < W; ++el) {
         const int j = column(el, r), k = nb * 16 + c;
         if (j >= p || k >= K) continue;
         const int64_t e = (int64_t)j * K + k;
@@ -373,9 +391,9 @@ __global__ __launch_bounds__(kWideWaves * 64, (sizeof(T) * NB <= 8 ? 3 : sizeof(
 
 template <typename T>
 int wide_chunk_cols() { return wide_chunk<T>(); }
-// Workgroups of the column-owner gradient for p columns.
-int wide_grad_groups(int64_t p, bool f64) {
-  const int64_t cols = (int64_t)kWideWaves * (f64 ? 32 : 64);
+// Workgroups of the column-owner gradient for p columns, by 16-byte loads or narrow.
+int wide_grad_groups(int64_t p, bool f64, bool narrow) {
+  const int64_t cols = (int64_t)kWideWaves * 16 * (narrow ? 1 : f64 ? 2 : 4);
   return (int)((p + cols - 1) / cols);
 }
 // Row slices wanted for p columns: about 512 / g with g the workgroups that hold at most 4 (2 in
@@ -396,14 +414,15 @@ int wide_logits_resident(int nb) { return nb == 1 ? 3 : nb == 2 ? 2 : 1; }
 
 template <typename T>
 hipError_t launch_wide(const WideArgs& a, int nb, int logits_tiles_y, int softmax_wg, int grad_wg,
-                       hipStream_t s) {
+                       bool narrow, hipStream_t s) {
   const dim3 lg(a.nchunk, logits_tiles_y);
   const dim3 gg(grad_wg, a.nsplit);
 #define HMC_WIDE(NB_)                                                                       \
   if (nb == NB_) {                                                                          \
     hipLaunchKernelGGL((wide_logits<T, NB_>), lg, dim3(kWideWaves * 64), 0, s, a);          \
     hipLaunchKernelGGL((wide_softmax<T, NB_>), dim3(softmax_wg), dim3(256), 0, s, a);       \
-    hipLaunchKernelGGL((wide_grad<T, NB_>), gg, dim3(kWideWaves * 64), 0, s, a);           \
+    if (narrow) hipLaunchKernelGGL((wide_grad<T, NB_, 1>), gg, dim3(kWideWaves * 64), 0, s, a); \
+    else hipLaunchKernelGGL((wide_grad<T, NB_, 16 / (int)sizeof(T)>), gg, dim3(kWideWaves * 64), 0, s, a); \
     return hipGetLastError();                                                               \
   }
   HMC_WIDE(1) HMC_WIDE(2) HMC_WIDE(4)
@@ -413,7 +432,7 @@ hipError_t launch_wide(const WideArgs& a, int nb, int logits_tiles_y, int softma
 
 template int wide_chunk_cols<float>();
 template int wide_chunk_cols<double>();
-template hipError_t launch_wide<float>(const WideArgs&, int, int, int, int, hipStream_t);
-template hipError_t launch_wide<double>(const WideArgs&, int, int, int, int, hipStream_t);
+template hipError_t launch_wide<float>(const WideArgs&, int, int, int, int, bool, hipStream_t);
+template hipError_t launch_wide<double>(const WideArgs&, int, int, int, int, bool, hipStream_t);
 
 }  // namespace hmcx

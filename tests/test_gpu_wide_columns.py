@@ -1,5 +1,5 @@
-"""Wide-p gradient (GPU tier) at the edges of its column spans (256 bytes of a row per wave, four
-waves per workgroup), row tiles and slices: remainders of both, odd tile counts per slice, padded
+"""Wide-p gradient (GPU tier) at the edges of its column spans (16 columns per wave, or 256 bytes of
+a row where the workgroups are many; four waves per workgroup), row tiles and slices: remainders of both, odd tile counts per slice, padded
 rows with NaN, every class-block count, both precisions, with the path forced. Bars: the
 element-wise bound of the row-sum rounding (16 u M) and rel-L2 1e-12 / 1e-5."""
 import numpy as np
@@ -16,6 +16,8 @@ pytestmark = pytest.mark.gpu
     (1, 1, 2, 0, 0), (15, 31, 3, 1, 0), (16, 32, 16, 0, 0), (17, 33, 17, 3, 0), (33, 63, 5, 0, 64), (64, 64, 33, 0, 64),
     (65, 65, 64, 5, 64), (100, 127, 4, 0, 0), (130, 129, 20, 0, 64), (200, 255, 7, 1, 128), (333, 257, 40, 0, 128),
     (79, 1025, 10, 2, 64), (48, 1023, 2, 0, 0), (500, 513, 16, 0, 192), (96, 2050, 12, 6, 0),
+    # workgroups enough for the wider spans (64 and 32 columns per wave)
+    (1300, 5103, 5, 0, 64), (1999, 4961, 20, 1, 64), (2001, 5000, 40, 0, 64),
 ])
 def test_span_edges(lib, n, p, K, pad, rows, f64):
     import torch
