@@ -253,10 +253,13 @@ hipError_t launch_one(const FusedArgs& a, int nwg, hipStream_t s) {
 // One free column, and columns that the lanes of half a wave hold: as many as the row tile takes.
 // Small problems stay with the row tile, whose waves have less to set up: float32, n = 50, p = 100:
 // 8.4 us against 8.9 (n = 1000: 10.0 against 9.6; n = 50, p = 192: 9.5 against 9.0); float64,
-// n = 5000, p = 100: 11.8 against 12.9.
-bool column_fits(int64_t n, int64_t p, int K, bool pin, bool f64) {
+// n = 5000, p = 100: 11.8 against 12.9. So do float64 probit problems of few columns: its link
+// function, here evaluated for two rows per wave, there for four, is then what takes the time
+// (n = 200000, p = 128: 84 us against 92; p = 384: 145 against 123).
+bool column_fits(int64_t n, int64_t p, int K, bool pin, bool f64, int link) {
   if ((pin ? K - 1 : K) != 1) return false;
-  return f64 ? p <= 512 && n * p >= (1 << 20) : p <= 1024 && (p > 128 || n >= 512);
+  if (!f64) return p <= 1024 && (p > 128 || n >= 512);
+  return p <= 512 && n * p >= (1 << 20) && (link != 2 || p > 256);
 }
 // A workgroup per compute unit, each wave with a pair of rows at least.
 int column_workgroups(int64_t n) {

@@ -364,7 +364,7 @@ __global__ __launch_bounds__(NW * 64) void fused_logpost_grad(FusedArgs a) {
   // all NW MB blocks take 1.7 of the 2.7 us per tile, in turn with the softmax, so 14 blocks of
   // 64 less (n = 60000, p = 785, K = 10, FP32) took 7 us from a pass of 45.
   // (Two variants have no registers to spare for the choice.)
-  constexpr bool SKIP = MB * NB < 16 && !(sizeof(T) == 8 && LINK == 2);
+  constexpr bool SKIP = MB * NB < 16 && !(sizeof(T) == 8 && LINK == 2 && MB == 4);
   const int live = ((p + 15) / 16 - w + NW - 1) / NW;
   if (SKIP && MB >= 2 && live <= MB / 2) run(std::integral_constant<int, SKIP && MB >= 2 ? MB / 2 : MB>{});
   else if (SKIP && MB >= 4 && live <= MB / 4 * 3) run(std::integral_constant<int, SKIP && MB >= 4 ? MB / 4 * 3 : MB>{});
