@@ -251,15 +251,16 @@ hipError_t launch_one(const FusedArgs& a, int nwg, hipStream_t s) {
 }  // namespace
 
 // One free column, and columns that the lanes of half a wave hold: as many as the row tile takes.
-// Small problems stay with the row tile, whose waves have less to set up: float32, n = 50, p = 100:
-// 8.4 us against 8.9 (n = 1000: 10.0 against 9.6; n = 50, p = 192: 9.5 against 9.0); float64,
-// n = 5000, p = 100: 11.8 against 12.9. So do float64 probit problems of few columns: its link
-// function, here evaluated for two rows per wave, there for four, is then what takes the time
-// (n = 200000, p = 128: 84 us against 92; p = 384: 145 against 123).
+// Small problems stay with the row tile, whose waves have less to set up: float32, n = 5000, p = 32:
+// 9.7 us against 10.0 (n = 20000: 12.0 against 11.3; n = 50, p = 192: 9.5 against 9.0); float64,
+// n = 27935, p = 51, K = 2: 20.4 against 22.1 (n = 20000, p = 128: 17.9 against 17.0). So do float64
+// probit problems of few columns: its link function, here evaluated for two rows per wave, there
+// for four, is then what takes the time (n = 200000, p = 128: 84 us against 92; p = 384: 145
+// against 123).
 bool column_fits(int64_t n, int64_t p, int K, bool pin, bool f64, int link) {
   if ((pin ? K - 1 : K) != 1) return false;
-  if (!f64) return p <= 1024 && (p > 128 || n >= 512);
-  return p <= 512 && n * p >= (1 << 20) && (link != 2 || p > 256);
+  if (!f64) return p <= 1024 && (p > 128 || n >= 8192);
+  return p <= 512 && n * p >= (p >= 256 ? 1 << 20 : 1 << 21) && (link != 2 || p > 256);
 }
 // A workgroup per compute unit, each wave with a pair of rows at least.
 int column_workgroups(int64_t n) {

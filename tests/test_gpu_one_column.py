@@ -11,10 +11,11 @@ import oracle
 pytestmark = pytest.mark.gpu
 # float64 problems are of the size from which the pass is taken
 SHAPES = [(False, n, p, pad) for n, p, pad in [
-    (1, 1025 - 1, 0), (2, 513, 0), (3, 1023, 1), (17, 512, 3), (33, 511, 0), (15, 1000, 8), (4099, 130, 2),
-    (2500, 65, 0), (9000, 15, 1), (70000, 3, 0), (5001, 769, 7), (20011, 17, 0)]] + [
+    (1, 1024, 0), (2, 513, 0), (3, 1023, 1), (17, 512, 3), (33, 511, 0), (15, 1000, 8), (4099, 130, 2),
+    (8200, 65, 0), (9000, 15, 1), (70000, 3, 0), (5001, 769, 7), (20011, 17, 0)]] + [
     (True, n, p, pad) for n, p, pad in [
-        (2048, 512, 0), (2053, 511, 1), (5463, 192, 0), (5491, 191, 3), (16400, 65, 2), (65537, 16, 0), (350001, 3, 0)]]
+        (2048, 512, 0), (2053, 511, 1), (4097, 257, 0), (10963, 192, 0), (10981, 191, 3), (32801, 65, 2), (131073, 16, 0),
+        (700001, 3, 0)]]
 
 
 @pytest.mark.parametrize("link", ["logit", "poisson", "probit"])
