@@ -305,11 +305,15 @@ __device__ __forceinline__ void logits_rows(const Job& j, int64_t rb, double (&l
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // X comes from branch-free buffer loads whose resource starts at the row block and ends at
-  // row n, so rows past n read as zero. Offsets fit 32 bits (ldx < 2^23). Instruction i loads
+  // X comes from branch-free buffer loads whose resource starts at the row block and ends with
+  // it or at row n, so rows past n read as zero. A block spans less than 2^31 bytes (ldx < 2^23),
+  // so the offset 0xFFFFFFF0 of a piece past column p lies beyond it however large X is: with all
+  // of X in the resource that offset fell inside a plane of more than 4 GiB, on any element or
+  // row padding there, whose NaN times a zero coefficient reached the logits. Instruction i loads
   // rows 8 i + lane / 8 of the wave's 32, 16-byte piece lane % 8 of the chunk.
   const int64_t rbase = rb * kHiloRows;
-  const uint64_t rem = (uint64_t)(n - rbase) * j.ldx * 2;
+  const int64_t brows = n - rbase < kHiloRows ? n - rbase : kHiloRows;
+  const uint64_t rem = (uint64_t)brows * j.ldx * 2;
   const __amdgpu_buffer_rsrc_t rh = make_rsrc(j.Xhi + rbase * j.ldx, rem);
   const __amdgpu_buffer_rsrc_t rl = make_rsrc(LO ? j.Xlo + rbase * j.ldx : j.Xhi, LO ? rem : 0);
   const int piece = lane & 7;
