@@ -150,7 +150,8 @@ __global__ __launch_bounds__(64 * kColumnWaves, 2) void column_pass(FusedArgs a)
       const T se = ez + e0;
       const T inv = dev_rcp(se), lse_shift = dev_log(se);
       res = (r.y == 0 ? T(1) : T(0)) - ez * inv;
-      l = (double)(((r.y == 0 ? z : z0) - mx) - lse_shift);
+      // as on the row tile: no term for a label outside the 16 padded classes
+      l = (unsigned)r.y < 16u ? (double)(((r.y == 0 ? z : z0) - mx) - lse_shift) : 0.0;
     }
     if (!valid) res = T(0);
     lacc += valid && hl == 0 ? l : 0.0;

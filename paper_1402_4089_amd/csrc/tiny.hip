@@ -204,7 +204,8 @@ __global__ __launch_bounds__(TH) void tiny_kernel(TinyArgs a) {
             res[tid * FP + k] = (k == yi ? T(1) : T(0)) - ex[k] * inv;
             zy = k == yi ? z[k] : zy;
           }
-        lacc = (double)((zy - mx) - lse_shift);
+        // as on the row tile: no term for a label outside the 16 padded classes
+        if ((unsigned)yi < 16u) lacc = (double)((zy - mx) - lse_shift);
       }
     }
     __syncthreads();
