@@ -174,7 +174,8 @@ hmc_status hmc_workspace_bytes(const hmc_problem* prob, size_t* bytes);
  * grid and row slices, for FP32/FP64 X; logits workgroups and gradient row slices of the
  * split-precision pass), each timed over repeated gradient evaluations at B with HIP events
  * on `stream`; writes the fastest to *out and its mean time per evaluation in microseconds
- * to *best_us (nullable). prob->tuning is ignored. ws must hold
+ * to *best_us (nullable). A small problem whose leapfrog updates the built-in rule runs in one
+ * workgroup keeps that rule. prob->tuning is ignored. ws must hold
  * hmc_autotune_workspace_bytes(prob) bytes (the largest candidate's workspace); G and
  * logpost receive the gradient and log K at B. Waits for the stream (host-synchronous). */
 hmc_status hmc_autotune_workspace_bytes(const hmc_problem* prob, size_t* bytes);
