@@ -2,10 +2,12 @@
 
 ``tuned(problem)`` returns the hmc_tuning for a Problem: from the cache when an entry for
 its key exists, otherwise measured on the device by the library's autotuner
-(hmc_autotune) and stored. The key is (X format, 16-class blocks, 16-column blocks,
-row-count bucket, link): every tuning in the cache is valid for every problem with that key
-(a row-tile variant covers the key's column blocks, and the other fields are counts that fit
-any row count). The cache is a JSON file at $HMC_TUNING_CACHE, or
+(hmc_autotune) and stored. The key is (library decomposition version, X format, 16-class blocks,
+16-column blocks, row-count bucket, link): every tuning in the cache is valid for every problem
+with that key (a row-tile variant covers the key's column blocks, and the other fields are counts
+that fit any row count). Where the built-in rule may choose the one-workgroup form or the
+one-column pass, the key holds n, p, K and the pinned class as they are: those choices depend
+on them, and an explicit tuning made for a neighbour would take them away. The cache is a JSON file at $HMC_TUNING_CACHE, or
 ~/.cache/paper_1402_4089_amd/tuning.json when that variable is unset; a cache that cannot
 be read or written is ignored (the tuning is then measured in every process).
 """
@@ -24,11 +26,20 @@ def cache_path() -> str:
     return os.path.join(os.path.expanduser("~"), ".cache", "paper_1402_4089_amd", "tuning.json")
 
 
+# Counts up when the library's built-in rule or its kernels change: what an earlier build
+# measured against them says nothing about this one.
+VERSION = 2
+
+
 def key_of(prob) -> str:
+    pin = int(getattr(getattr(prob, "desc", None), "pin_last_class", 0))
+    # sizes that the one-workgroup form or the one-column pass may take (FP64 and FP32 X)
+    if prob.xfmt in (0, 1) and ((prob.n <= 1024 and prob.p <= 256 and prob.K <= 16) or prob.K - pin == 1):
+        return f"v={VERSION}:xfmt={prob.xfmt}:n={prob.n}:p={prob.p}:K={prob.K}:pin={pin}:link={prob.link}"
     nb = (prob.K + 15) // 16
     nblk = (prob.p + 15) // 16
     nbucket = 1 << max(0, int(prob.n - 1).bit_length())       # n rounded up to a power of two
-    return f"xfmt={prob.xfmt}:nb={nb}:nblk={nblk}:n<={nbucket}:link={prob.link}"
+    return f"v={VERSION}:xfmt={prob.xfmt}:nb={nb}:nblk={nblk}:n<={nbucket}:link={prob.link}"
 
 
 def _read(path: str) -> dict:
