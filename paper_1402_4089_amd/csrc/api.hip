@@ -322,8 +322,8 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
   L->off_bp = off;    off = align_up(off + (size_t)pk * L->ts);
   L->off_gp = off;    off = align_up(off + (size_t)pk * L->ts);
   L->off_scal = off;  off = align_up(off + 8 * sizeof(double));
-  L->off_ctr = off;   off = align_up(off + 2 * sizeof(int64_t));
-  L->off_ticket = off; off = align_up(off + sizeof(uint32_t));
+  L->off_ctr = off;
+  L->off_ticket = off + 2 * sizeof(int64_t); off = align_up(L->off_ticket + sizeof(uint32_t));
   // more partials than one epilogue workgroup per element takes, and few workgroups to count
   L->last_sum = L->column && L->nwg > kEpiFewMax && L->nepi <= 64;
   L->total = off;
@@ -1051,7 +1051,10 @@ hmc_status hmc_logpost_grad(const hmc_problem* prob, const void* B, double* logp
 // names a host-side stand-in; its device address comes from hipGetSymbolAddress, taken
 // once per device with that device current, and only that address is passed to kernels.
 namespace {
-constexpr size_t kScratchBytes = (size_t)32 << 20;
+// 32 MiB, and what the wide-p path's workspace takes since its residuals come in whole 16-row tiles
+// (at most 15 rows of 64 doubles, and the partial sums of more workgroups): problems that filled the
+// 32 MiB before still fit.
+constexpr size_t kScratchBytes = ((size_t)32 << 20) + (16 << 10);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
