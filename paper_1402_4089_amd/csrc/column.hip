@@ -243,10 +243,14 @@ constexpr int kStreamCols = 192, kNonTemporal = 2;
 
 template <typename T, int MBL, int LINK>
 hipError_t launch_one(const FusedArgs& a, int nwg, hipStream_t s) {
-  if constexpr (sizeof(T) == 8) {
-    if (a.p >= kStreamCols) return launch_variant<T, MBL, LINK, kNonTemporal>(a, nwg, s);
+  if constexpr (sizeof(T) == 8 && LINK == 2) {    // more than 256 columns (column_fits)
+    return launch_variant<T, MBL, LINK, kNonTemporal>(a, nwg, s);
+  } else {
+    if constexpr (sizeof(T) == 8) {
+      if (a.p >= kStreamCols) return launch_variant<T, MBL, LINK, kNonTemporal>(a, nwg, s);
+    }
+    return launch_variant<T, MBL, LINK, 0>(a, nwg, s);
   }
-  return launch_variant<T, MBL, LINK, 0>(a, nwg, s);
 }
 
 }  // namespace

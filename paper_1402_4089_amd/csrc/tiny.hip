@@ -309,7 +309,7 @@ hipError_t launch_one(const TinyArgs& a, size_t lds, hipStream_t s) {
 bool tiny_fits(int64_t n, int64_t p, int K, bool pin, bool f64, bool update) {
   if (n > 1024 || p > 256 || K > 16 || p * K > 1024 || n * p * K > (int64_t)1 << 16) return false;
   const int fp = class_pad(pin ? K - 1 : K);
-  if (p * fp > 512) return false;
+  if (p * fp > 512 || (fp == 16 && n > 512)) return false;   // 16 classes: 512 threads (the times below say no more)
   const double N = (double)n, P = (double)p, F = fp, far = p > 128 ? 1.2 : 0.0;   // far: a wider row tile
   const double here =
       update ? (f64 ? 1.7 + P * (0.024 + 0.0116 * F) + N * (0.0010 + 0.00125 * F)
@@ -328,8 +328,9 @@ hipError_t launch_tiny(const TinyArgs& a, hipStream_t s) {
   const size_t lds = tiny_layout((int)a.n, a.p, fp, th, sizeof(T)).total;
 #define HMC_TINY(FP_)                                                                        \
   if (fp == FP_) return th == 512 ? launch_one<T, FP_, 512>(a, lds, s) : launch_one<T, FP_, 1024>(a, lds, s);
-  HMC_TINY(1) HMC_TINY(2) HMC_TINY(4) HMC_TINY(8) HMC_TINY(16)
+  HMC_TINY(1) HMC_TINY(2) HMC_TINY(4) HMC_TINY(8)
 #undef HMC_TINY
+  if (fp == 16 && th == 512) return launch_one<T, 16, 512>(a, lds, s);
   return hipErrorInvalidValue;
 }
 
