@@ -204,7 +204,7 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
     L->nwg = (int)((L->ntiles + per - 1) / per);
   }
   if ((int64_t)L->nwg > L->ntiles) L->nwg = (int)L->ntiles;
-  L->column = !L->wide && !L->hilo && tu.path == 0 && column_fits(pr->n, pr->p, pr->K, pr->pin_last_class != 0, L->f64, pr->link);
+  L->column = !L->wide && !L->hilo && tu.path == 0 && column_fits(pr->n, pr->p, pr->K, pr->pin_last_class != 0, L->f64, pr->link, pr->ldx);
   if (L->column) L->nwg = column_workgroups(pr->n);
   const int64_t pk = pr->p * (int64_t)pr->K;
   L->nepi = (int)((pk + kEpiElems - 1) / kEpiElems);

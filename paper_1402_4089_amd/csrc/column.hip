@@ -256,15 +256,23 @@ hipError_t launch_one(const FusedArgs& a, int nwg, hipStream_t s) {
 }  // namespace
 
 // One free column, and columns that the lanes of half a wave hold: as many as the row tile takes.
-// Small problems stay with the row tile, whose waves have less to set up: float32, n = 5000, p = 32:
-// 9.7 us against 10.0 (n = 20000: 12.0 against 11.3; n = 50, p = 192: 9.5 against 9.0); float64,
-// n = 27935, p = 51, K = 2: 20.4 against 22.1 (n = 20000, p = 128: 17.9 against 17.0). So do float64
-// probit problems of few columns: its link function, here evaluated for two rows per wave, there
-// for four, is then what takes the time (n = 200000, p = 128: 84 us against 92; p = 384: 145
-// against 123).
-bool column_fits(int64_t n, int64_t p, int K, bool pin, bool f64, int link) {
+// The row tile keeps (us here against there)
+//  - small problems, whose waves have less to set up there: float32, n = 5000, p = 32: 10.0 against 9.7
+//    (n = 20000: 11.3 against 12.0; n = 50, p = 192: 9.0 against 9.5); float64, n = 27935, p = 51, K = 2:
+//    22.1 against 20.4 (n = 20000, p = 128: 17.0 against 17.9);
+//  - rows of a few floats, of which a wave here takes two and a tile there sixteen, below the sizes
+//    where that tells: Poisson, five updates, p = 3: n = 15000 51.5 against 48.1, n = 60000 83.1 against
+//    80.9, n = 120000 124 against 127; p = 6: n = 10000 49.6 against 47.0, n = 15000, p = 5: 50.5 against 51.7;
+//  - float64 probit problems of few columns: its link function, here evaluated for two rows per wave,
+//    there for four, is then what takes the time (n = 200000, p = 128: 92 against 84; p = 384: 123
+//    against 145);
+//  - float64 two-class problems of up to 128 columns in odd number without row padding, whose rows
+//    start off 16-byte pieces here while the tile there needs no mask: n = 92307, p = 65: 44.4 against
+//    41.4 (with a padded row 43.8 against 46.7; p = 151: 57.9 against 72.6).
+bool column_fits(int64_t n, int64_t p, int K, bool pin, bool f64, int link, int64_t ldx) {
   if ((pin ? K - 1 : K) != 1) return false;
-  if (!f64) return p <= 1024 && (p > 128 || n >= 8192);
+  if (!f64) return p <= 1024 && (p > 128 || n >= (p < 4 ? 65536 : p < 16 ? 16384 : 8192));
+  if (link == 0 && p <= 128 && p % 2 && ldx == p) return false;
   return p <= 512 && n * p >= (p >= 256 ? 1 << 20 : 1 << 21) && (link != 2 || p > 256);
 }
 // A workgroup per compute unit, each wave with a pair of rows at least.

@@ -258,7 +258,7 @@ template <typename T>
 hipError_t launch_fused(const FusedArgs& a, int nwg, int waves, int mb, int nb, size_t lds,
                         hipStream_t s);
 // One-column pass: does it take the problem, and with how many workgroups (partials)?
-bool column_fits(int64_t n, int64_t p, int K, bool pin, bool f64, int link);
+bool column_fits(int64_t n, int64_t p, int K, bool pin, bool f64, int link, int64_t ldx);
 int column_workgroups(int64_t n);
 template <typename T> hipError_t launch_column(const FusedArgs& a, int nwg, hipStream_t s);
 template <typename T> hipError_t launch_epilogue(const EpiArgs& a, int nwg, hipStream_t s);
