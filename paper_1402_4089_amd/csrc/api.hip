@@ -282,7 +282,14 @@ hmc_status make_layout(const hmc_problem* pr, Layout* L) {
     // 442, 397; n = 10000, p = 5000, K = 20, 260 workgroups: 464, 517; n = 20000, p = 1100, K = 10,
     // 395: 272, 290. FP64: n = 500, p = 1500, K = 50, 96: 150, 138; n = 8000, p = 700, K = 30, 252:
     // 220, 229)
-    L->narrow = (int64_t)wide_grad_groups(pr->p, L->f64, false) * L->wsplit <= (L->f64 ? 128 : L->nb == 4 ? 512 : 256);
+    // Between 256 and 320 a few compute units get a second workgroup, whose time is all that wider spans
+    // cost where the slices are short or many (five updates, wide against narrow, FP32: n = 1402, p = 2908,
+    // K = 32, 264 workgroups: 172, 160; n = 25740, p = 867, K = 24, 272: 375, 339; but n = 10000, p = 5000
+    // above. FP64: n = 55074, p = 297, K = 48, 288: 1023, 864); with one class block both take the same.
+    const int64_t spans = (int64_t)wide_grad_groups(pr->p, L->f64, false) * L->wsplit;
+    const int64_t slice = L->wsplit > 1 ? L->wtps : L->ntiles;
+    L->narrow = spans <= (L->f64 ? 128 : L->nb == 4 ? 512 : 256) ||
+                (L->nb > 1 && spans > 256 && spans <= 320 && (slice <= 8 || L->wsplit >= 24));
     L->ngrad = wide_grad_groups(pr->p, L->f64, L->narrow);
     L->nl = L->nsoft;
     L->np = L->wsplit > 1 ? L->nepi : L->ngrad;
