@@ -11,6 +11,7 @@
 // X^T R over a slice of rows each, and the shared epilogue sums the slices.
 #include <math.h>
 
+#include <algorithm>
 #include <utility>
 
 #include "device_common.h"
@@ -58,16 +59,21 @@ __device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
 
 // ---------------------------------------------------------------------------------------
 // Encoding of X: one thread per 8 output columns of a row; columns [p, ldo) are zeroed. Memory
-// bounds it: sizeof(Tin) bytes read and 2 or 4 written per element. A workgroup takes `rows`
-// whole rows (about kSplitGroups groups of 8), a thread kSplitUnroll groups at a time, all of
-// whose loads are issued before the first conversion. The differences x - hi are exact in the
-// type of X (hi holds the leading bits of x), so FP32 X is encoded in FP32: both planes have
-// the bits of the conversion through float64, a NaN's sign and quiet bit included. Measured, n =
-// 50000, p = 4096, FP32 to both planes: 297 us (5.5 TB/s; a device copy of that size reaches
-// 4.8), against 596 us with one group per thread in flight, element loads, a 64-bit division
-// per group and integer rounding of doubles.
-constexpr int kSplitUnroll = 4, kSplitGroups = 256 * kSplitUnroll * 2;
-constexpr int64_t kSplitSpan = 1 << 20;          // column groups of one grid row
+// bounds it: sizeof(Tin) bytes read and 2 or 4 written per element. A workgroup takes `rows` rows of
+// `span` groups of 8 columns, a thread UNROLL groups at a time, all of whose loads are issued before
+// the first conversion. The differences x - hi are exact in the type of X (hi holds the leading bits
+// of x), so FP32 X is encoded in FP32: both planes have the bits of the conversion through float64, a
+// NaN's sign and quiet bit included. Measured, n = 50000, p = 4096, FP32 to both planes: 297 us (5.5
+// TB/s; a device copy of that size reaches 4.8), against 596 us with one group per thread in flight,
+// element loads, a 64-bit division per group and integer rounding of doubles.
+//
+// A workgroup has kSplitGroups groups of whole rows, two rounds of four per thread, where that makes
+// kSplitWorkgroups of them or more. A smaller X takes a round's latency, not the rate: fewer groups
+// per workgroup then, down to one per thread, and pieces of the rows; so do fewer than 8 columns,
+// whose groups are padding but one per row (us with one group per thread against two rounds of
+// four: n = 3027, p = 366, FP64: 4.9, 13.4; n = 17041, p = 1, FP32: 3.2, 8.6).
+constexpr int kSplitUnroll = 4, kSplitGroups = 256 * kSplitUnroll * 2, kSplitWorkgroups = 2048;
+constexpr int64_t kSplitSpan = 1 << 20;          // column groups of one grid row at most
 
 __device__ __forceinline__ void split_one(double x, u16& h, u16& l) {
   h = bf16_from_f64(x);
@@ -81,20 +87,21 @@ __device__ __forceinline__ void split_one(float x, u16& h, u16& l) {
   l = bf16_quiet(x - f32_from_bf16(h));
 }
 
-template <typename Tin>
+template <typename Tin, int UNROLL>
 __global__ __launch_bounds__(256) void split_kernel(const Tin* __restrict__ X, int64_t ldx,
                                                     int64_t n, int64_t p, u16* __restrict__ hi,
-                                                    u16* __restrict__ lo, int64_t ldo, uint32_t rows) {
+                                                    u16* __restrict__ lo, int64_t ldo, uint32_t rows,
+                                                    int64_t span) {
   struct alignas(sizeof(Tin)) Run { Tin v[8]; };      // 8 elements at any element address
   const int64_t r0 = (int64_t)blockIdx.x * rows;
-  const int64_t g0 = (int64_t)blockIdx.y * kSplitSpan;   // first column group of this workgroup
-  const uint32_t gpr = (uint32_t)(ldo / 8 - g0 < kSplitSpan ? ldo / 8 - g0 : kSplitSpan);
+  const int64_t g0 = (int64_t)blockIdx.y * span;      // first column group of this workgroup
+  const uint32_t gpr = (uint32_t)(ldo / 8 - g0 < span ? ldo / 8 - g0 : span);
   const uint32_t total = (uint32_t)(n - r0 < rows ? n - r0 : rows) * gpr;
-  for (uint32_t t0 = threadIdx.x; t0 < total; t0 += 256 * kSplitUnroll) {
-    Run x[kSplitUnroll];
-    int64_t row[kSplitUnroll], c0[kSplitUnroll];
+  for (uint32_t t0 = threadIdx.x; t0 < total; t0 += 256 * UNROLL) {
+    Run x[UNROLL];
+    int64_t row[UNROLL], c0[UNROLL];
 #pragma unroll
-    for (int u = 0; u < kSplitUnroll; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
       const uint32_t t = t0 + 256 * u, i = t / gpr;
       row[u] = r0 + i;
       c0[u] = (g0 + (t - i * gpr)) * 8;
@@ -107,11 +114,19 @@ __global__ __launch_bounds__(256) void split_kernel(const Tin* __restrict__ X, i
       }
     }
 #pragma unroll
-    for (int u = 0; u < kSplitUnroll; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
       if (t0 + 256 * u >= total) break;
       u16 h[8], l[8];
+      if (UNROLL > 1 || p >= 8) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) split_one(x[u].v[j], h[j], l[j]);
+        for (int j = 0; j < 8; ++j) split_one(x[u].v[j], h[j], l[j]);
+      } else {                                        // all else is padding
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          h[j] = l[j] = 0;
+          if (j < p) split_one(x[u].v[j], h[j], l[j]);
+        }
+      }
       const int64_t o = row[u] * ldo + c0[u];
       *reinterpret_cast<u32x4*>(hi + o) =
           u32x4{pack2(h[0], h[1]), pack2(h[2], h[3]), pack2(h[4], h[5]), pack2(h[6], h[7])};
@@ -790,12 +805,17 @@ __global__ __launch_bounds__(64 * NW, 2) void batch_grad(BatchArgs a) {
 template <typename Tin>
 hipError_t launch_split(const Tin* X, int64_t ldx, int64_t n, int64_t p, uint16_t* hi,
                         uint16_t* lo, int64_t ldo, hipStream_t s) {
-  // whole rows per workgroup; grids beyond 2^31 workgroups take more rows each
-  int64_t rows = kSplitGroups / (ldo / 8);
-  const int64_t least = (n + 0x3FFFFFFF) / 0x40000000;
-  rows = rows < least ? least : rows;
-  const dim3 grid((unsigned)((n + rows - 1) / rows), (unsigned)((ldo / 8 + kSplitSpan - 1) / kSplitSpan));
-  hipLaunchKernelGGL(split_kernel<Tin>, grid, dim3(256), 0, s, X, ldx, n, p, hi, lo, ldo, (uint32_t)rows);
+  // groups per workgroup; grids beyond 2^31 workgroups take more rows each
+  const int64_t gpr = ldo / 8, all = n * gpr;
+  const int64_t fit = p < 8 ? 256 : std::max<int64_t>(256, all / kSplitWorkgroups / 256 * 256);
+  const int64_t want = std::min<int64_t>(kSplitGroups, fit);
+  const int64_t span = want < kSplitGroups && gpr > want ? std::max(want, (gpr + 0x7FFF) / 0x8000) : std::min(gpr, kSplitSpan);
+  const int64_t rows = std::max<int64_t>({1, want / gpr, (n + 0x3FFFFFFF) / 0x40000000});
+  const dim3 grid((unsigned)((n + rows - 1) / rows), (unsigned)((gpr + span - 1) / span));
+  if (want == 256)
+    hipLaunchKernelGGL((split_kernel<Tin, 1>), grid, dim3(256), 0, s, X, ldx, n, p, hi, lo, ldo, (uint32_t)rows, span);
+  else
+    hipLaunchKernelGGL((split_kernel<Tin, kSplitUnroll>), grid, dim3(256), 0, s, X, ldx, n, p, hi, lo, ldo, (uint32_t)rows, span);
   return hipGetLastError();
 }
 template hipError_t launch_split<float>(const float*, int64_t, int64_t, int64_t, uint16_t*, uint16_t*, int64_t, hipStream_t);
