@@ -18,7 +18,12 @@
 //            layout would need 4 K accumulators per lane and more.
 // Measured at the size above: 287 us, against 7990 us with the logits on the vector unit (each
 // sample's coefficients staged in LDS by every tile, one multiply-add per two LDS reads).
+// Few samples leave columns of the matrix and waves without work, and the registers leave a
+// compute unit one to three workgroups; the vector-unit form (predict_rows) then stays, where
+// rows_faster says so: n = 16607, p = 41, K = 14, S = 1 takes 7.1 us there and 65.4 here.
 #include <math.h>
+
+#include <algorithm>
 
 #include "device_common.h"
 
@@ -335,16 +340,149 @@ __global__ __launch_bounds__(256) void predict_classes(PredictArgs a) {
   }
 }
 
+// Few samples, or rows of a few columns and many tiles: thread (r, c) = (tid / 16, tid % 16) of a
+// 16-row tile forms the logits of row r for classes c, c + 16, .. of one sample after the other, whose
+// coefficients are staged in LDS in turn (the 16 lanes of a row are one DPP row). Two LDS reads
+// per multiply-add bound it; eight workgroups fit a compute unit while the LDS holds them.
+template <typename T, int NB>
+__global__ __launch_bounds__(256) void predict_rows(PredictArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* xs = reinterpret_cast<T*>(smem);                       // [16][p]
+  T* bs = xs + 16 * (int64_t)a.p;                           // [p][K] of the current sample
+  const int tid = threadIdx.x, r = tid >> 4, c = tid & 15;
+  const int p = a.p, K = a.K;
+  const int kmax = a.pin ? K - 1 : K;
+  const int64_t n = a.n, ldx = a.ldx;
+  const T* X = static_cast<const T*>(a.X);
+  const T* S = static_cast<const T*>(a.samples);
+  const int64_t pk = (int64_t)p * K;
+  for (int64_t tile = blockIdx.x; tile * 16 < n; tile += gridDim.x) {
+    const int64_t i0 = tile * 16;
+    __syncthreads();                                        // previous tile's readers done
+    for (int64_t e = tid; e < 16 * (int64_t)p; e += 256) {
+      const int64_t rr = e / p, j = e - rr * p;
+      xs[e] = (i0 + rr < n) ? X[(i0 + rr) * ldx + j] : T(0);
+    }
+    double acc[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) acc[q] = 0.0;
+    for (int s = 0; s < a.n_samples; ++s) {
+      __syncthreads();                                      // previous sample's readers done
+      const T* Bs = S + (int64_t)s * pk;
+      for (int64_t e = tid; e < pk; e += 256) bs[e] = Bs[e];
+      __syncthreads();
+      T z[NB];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) z[q] = T(0);
+      const T* xr = xs + (int64_t)r * p;
+      for (int j = 0; j < p; ++j) {
+        const T xv = xr[j];
+        const T* br = bs + (int64_t)j * K;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+          const int k = 16 * q + c;
+          z[q] += xv * (k < kmax ? br[k] : T(0));
+        }
+      }
+      // softmax over the K classes of row r (the pinned class, if any, keeps logit 0)
+      T mx = -INFINITY;
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        if (16 * q + c < K) mx = fmax(mx, z[q]);
+      mx = max16(mx);
+      T ex[NB], se = T(0);
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        ex[q] = (16 * q + c < K) ? exp(z[q] - mx) : T(0);
+        se += ex[q];
+      }
+      se = sum16(se);
+#pragma unroll
+      for (int q = 0; q < NB; ++q) acc[q] += (double)ex[q] / (double)se;
+    }
+    // mean probabilities and the class of the largest (lowest index among exact ties)
+    const int64_t i = i0 + r;
+    const double inv = 1.0 / (double)a.n_samples;
+    double best = -1.0;
+    int bk = 0;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const int k = 16 * q + c;
+      const double m = acc[q] * inv;
+      if (k < K && i < n && a.mean_prob) a.mean_prob[i * K + k] = m;
+      if (k < K && m > best) { best = m; bk = k; }
+    }
+    // argmax across the 16 lanes of the row: compare (value, -index) pairs
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) {
+      const double ob = __shfl_xor(best, m, 64);
+      const int ok = __shfl_xor(bk, m, 64);
+      if (ob > best || (ob == best && ok < bk)) { best = ob; bk = ok; }
+    }
+    if (c == 0 && i < n && a.classes) a.classes[i] = bk;
+  }
+}
+
+template <typename T, int NB>
+hipError_t launch_rows(const PredictArgs& a, hipStream_t s) {
+  const int64_t tiles = (a.n + 15) / 16;
+  const size_t lds = predict_lds_bytes(a.p, a.K, sizeof(T) == 8);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&predict_rows<T, NB>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((predict_rows<T, NB>), dim3((unsigned)(tiles < 16384 ? tiles : 16384)), dim3(256), lds, s, a);
+  return hipGetLastError();
+}
+
+size_t matrix_lds(int64_t p, int waves, int nb, size_t ts) {
+  const size_t tile = 16 * (size_t)tile_pitch(p, ts) * ts, sums = (size_t)waves * 16 * 16 * nb * 8;
+  return tile > sums ? tile : sums;
+}
+
 template <typename KERN>
 hipError_t launch_kernel(KERN kernel, const PredictArgs& a, int waves, int nb, size_t ts, hipStream_t s) {
-  const size_t tile = 16 * (size_t)tile_pitch(a.p, ts) * ts, sums = (size_t)waves * 16 * 16 * nb * 8;
-  const size_t lds = tile > sums ? tile : sums;
+  const size_t lds = matrix_lds(a.p, waves, nb, ts);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   const int64_t tiles = (a.n + 15) / 16;
   hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles < (1 << 20) ? tiles : (1 << 20))), dim3(64 * waves), lds, s, a);
   return hipGetLastError();
+}
+
+// Is the vector-unit form the faster one? Both times follow from a tile's and the workgroups that a
+// compute unit holds at once, here in us as fitted to 6400 sizes (n <= 400000, p <= 2200, up to 200
+// samples; 90% within 20%), so that the choice is slower than the other form by more than 3% at 2%
+// of them. With u tiles per compute unit, w workgroups of the form at once, f blocks of a matrix step
+// (free classes up to 16 classes, then 16 classes each) and g turns of a wave's sample groups:
+//   rows    3.3 + (r4 p + S (r0 + r1 p ceil(K / 16) + r2 p K)) (max(1, u / w) + r3 u)
+//   matrix  m0 + (m1 f + g (m2 + m3 f + ceil(p / 4) (m4 + m5 f))) ceil(u / w) (1 + m6 (min(u, w) - 1))
+// The rows also get what they lose by less than 5% (10% beyond 16 classes), about what the fit is
+// off where the two cross.
+struct FormTimes { double r[5], m[7]; };
+constexpr FormTimes kFormTimes[2][2] = {
+  {{{0.343, 0.0376, 0.00041, 0.104, 0.0189}, {1.82, 0.384, 3.44, 0.0, 0.0542, 0.0243, 0.149}},
+   {{0.386, 0.0203, 0.00056, 0.135, 0.0119}, {3.46, 0.641, 0.958, 0.470, 0.0349, 0.0724, 0.415}}},
+  {{{0.456, 0.0407, 0.00033, 0.157, 0.0226}, {2.07, 0.533, 3.06, 0.0508, 0.0221, 0.0506, 0.267}},
+   {{0.568, 0.0177, 0.00084, 0.223, 0.0112}, {2.70, 0.881, 1.14, 0.845, 0.0731, 0.0963, 0.435}}}};
+
+bool rows_faster(const PredictArgs& a, bool f64) {
+  const size_t ts = f64 ? 8 : 4;
+  const bool wide = a.K > 16;
+  const FormTimes& t = kFormTimes[f64][wide];
+  const int nb = (a.K + 15) / 16, F = a.pin ? a.K - 1 : a.K;
+  const int most = F <= (f64 ? 4 : 9) ? 8 : 4, waves = !wide && a.n_samples > 64 ? most : 4;
+  // waves per SIMD that the matrix form's registers allow
+  const int occ = wide ? (nb <= (f64 ? 2 : 3) ? 2 : 1) : !f64 && F <= 3 ? 3 : F <= (f64 ? 4 : 9) ? 2 : 1;
+  const double p = a.p, S = a.n_samples, u = (double)((a.n + 15) / 16) / 256.0, f = wide ? nb : F;
+  const double lds = 160.0 * 1024.0;
+  const double wr = std::clamp(floor(lds / (double)(predict_lds_bytes(a.p, a.K, f64) + 1)), 1.0, 8.0);
+  const double wm = std::max(1.0, std::min((double)(4 * occ / waves), floor(lds / (double)(matrix_lds(a.p, waves, wide ? nb : 1, ts) + 64))));
+  const double g = ceil(ceil(S / (wide ? 2.0 : 16.0)) / waves), u1 = std::max(u, 1.0);
+  const double rows = 3.3 + (t.r[4] * p + S * (t.r[0] + t.r[1] * p * nb + t.r[2] * p * a.K)) * (std::max(1.0, u / wr) + t.r[3] * u);
+  const double matrix = t.m[0] + (t.m[1] * f + g * (t.m[2] + t.m[3] * f + ceil(p / 4.0) * (t.m[4] + t.m[5] * f))) *
+                                     ceil(u1 / wm) * (1.0 + t.m[6] * (std::min(u1, wm) - 1.0));
+  return rows < (wide ? 1.10 : 1.05) * matrix;
 }
 
 // Eight waves where two fit a SIMD and there are more than four groups of samples to share out.
@@ -356,12 +494,22 @@ hipError_t launch_samples(const PredictArgs& a, hipStream_t s) {
 
 }  // namespace
 
+// A 16-row tile and one sample: what predict_rows holds, and the bound of the call. It leaves p <= 2275
+// in FP32 and 1137 in FP64, so the matrix forms' tile of whole 64-column groups takes 148 KB at most.
 size_t predict_lds_bytes(int64_t p, int K, bool f64) {
   return (size_t)(16 * p + p * K) * (f64 ? 8 : 4);
 }
 
 template <typename T>
 hipError_t launch_predict(const PredictArgs& a, hipStream_t s) {
+  if (rows_faster(a, sizeof(T) == 8)) {
+    switch ((a.K + 15) / 16) {
+      case 1: return launch_rows<T, 1>(a, s);
+      case 2: return launch_rows<T, 2>(a, s);
+      case 3: return launch_rows<T, 3>(a, s);
+      case 4: return launch_rows<T, 4>(a, s);
+    }
+  }
   if (a.K <= 16) {
     switch (a.pin ? a.K - 1 : a.K) {
 #define HMC_PRED(F_) case F_: return launch_samples<T, F_>(a, s);
