@@ -699,7 +699,7 @@ int batch_grad_waves(const hmc_problem* probs, int32_t n_prob, int rows) {
 
 struct BatchLayout {
   int nprob = 0, chains = 0, group = 1;   // group: 16-class blocks per chain
-  bool lo = false;
+  bool lo = false, few = false;           // few: every problem has few_rows rows at most
   int gwaves = 8;                         // waves of a gradient workgroup
   int rows = kBatchDefaultRows, grid = kBatchDefaultGrid;
   std::vector<BatchProb> table;           // entry t describes problem order[t]
@@ -756,6 +756,8 @@ hmc_status make_batch_layout(const hmc_problem* probs, int32_t n_prob, int32_t c
   B->group = batch_group(probs, n_prob);
   const int blocks = chains * B->group;
   B->lo = probs[0].xfmt == HMC_X_BF16_HILO;
+  B->few = true;
+  for (int b = 0; b < n_prob; ++b) B->few &= probs[b].n <= few_rows(blocks);
   B->table.assign(n_prob, BatchProb{});
   // Work items are numbered problem by problem in decreasing order of p (the cost of a
   // logits row block): the largest items start first and the smallest fill the tail.
@@ -885,7 +887,7 @@ hmc_status batch_gradient(const BatchLayout& BL, BatchArgs a, int mode, hipStrea
                        persistent_grid(BL.first[1][BL.nprob], BL.grid),
                        persistent_grid(xcd_span(BL.first[2][BL.nprob], grad_chunk(BL.gwaves)), BL.grid)};
   HMC_TRY(timed_launch(s, true, [&] {
-    return hip_status(launch_batch_pass(a, BL.chains, BL.group, BL.lo, BL.gwaves, grid, pack, s), "batched split-precision pass");
+    return hip_status(launch_batch_pass(a, BL.chains, BL.group, BL.lo, BL.few, BL.gwaves, grid, pack, s), "batched split-precision pass");
   }));
   return hip_status(launch_batch_epilogue(a, (int)BL.n_epi, s), "batched epilogue");
 }

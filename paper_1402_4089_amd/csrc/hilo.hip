@@ -470,6 +470,140 @@ __device__ __forceinline__ void logits_rows(const Job& j, int64_t rb, double (&l
   softmax_residuals<NB, GROUP>(j, rb, acc, ylab, lacc);
 }
 
+// The logits of a problem of few rows, which are one workgroup's: the latency of its chain of k steps
+// bounds them, not the reading of X. The A operand comes straight from global memory, kFewSteps - 1 k
+// steps ahead of the MFMAs: lane l loads the 8 consecutive columns 32 s + 8 (l / 16) .. of row l % 16
+// of each M block, the A input layout, without the turn through LDS that whole lines take in
+// logits_rows. B as there; same order of sums. A gradient with hi + lo planes, here and there: n = 12,
+// p = 5620, K = 33 83 and 117 us; n = 31, p = 11617, K = 20 101 and 147. With more rows the lines
+// gain on it (p of 1500 to 14000, K = 8, n = 80: 0.98 of the time and 0.90, n = 88: 0.98 and 0.85; K = 50,
+// whose B chunks are half as long there, n = 88: 0.93 and 1.16, n = 128: 0.96 and 1.01).
+constexpr int kFewSteps = 4;
+template <int NB> constexpr int few_lds_elems() { return 2 * kFewSteps * NB * 1024; }
+template <int NB, int GROUP, bool LO>
+__device__ __forceinline__ void logits_few_rows(const Job& j, double (&lacc)[NB / GROUP], u16* __restrict__ bs) {
+  constexpr int CH = kFewSteps * NB * 1024;         // u16 per chunk (hi and lo fragments)
+  constexpr int PER = CH / 8 / (kHiloWaves * 64);   // 16-byte pieces per thread per chunk
+  static_assert(CH / 8 % (kHiloWaves * 64) == 0, "a B chunk is a whole number of 16-byte pieces per thread");
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = lane & 15, g = lane >> 4;
+  const int64_t n = j.n;
+  const int p = j.p;
+  const int nks = (p + 31) / 32;
+  constexpr int MB = kHiloMB;
+  f32x4 acc[MB][NB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // X fragments come from branch-free buffer loads whose resource ends at row n, so rows past
+  // n read as zero; columns past p are zeroed in registers on the last (ragged) k step.
+  const uint64_t rem = (uint64_t)n * j.ldx * 2;
+  const __amdgpu_buffer_rsrc_t rh = make_rsrc(j.Xhi, rem);
+  const __amdgpu_buffer_rsrc_t rl = make_rsrc(LO ? j.Xlo : j.Xhi, LO ? rem : 0);
+  uint32_t xoff[MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+    xoff[mb] = (uint32_t)(((int64_t)(w * 16 * MB + 16 * mb + m) * j.ldx + 8 * g) * 2);
+  // labels of this lane's rows, loaded now so their latency hides behind the k loop
+  // (rows past n read as zero and are not used)
+  const __amdgpu_buffer_rsrc_t yres = make_rsrc(j.y, (uint64_t)n * 4);
+  int ylab[MB][4];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      ylab[mb][i] = __builtin_amdgcn_raw_buffer_load_b32(
+          yres, (int)((w * 16 * MB + 16 * mb + 4 * g + i) * 4), 0, 0);
+  const int nch = (nks + kFewSteps - 1) / kFewSteps;
+  const int64_t bp_total = (int64_t)nks * NB * 1024;
+  u32x4 bst[PER];
+  // every load below is issued unconditionally: buffer loads past a resource's end read
+  // zero, and straight-line issue keeps the compiler's load counting exact (a load under a
+  // branch makes it wait for everything at the join)
+  const __amdgpu_buffer_rsrc_t bres = make_rsrc(j.Bpk, (uint64_t)bp_total * 2);
+  auto fetch_b = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int64_t idx = (int64_t)c * CH + (int64_t)(i * kHiloWaves * 64 + threadIdx.x) * 8;
+      bst[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(bres, (int)(idx * 2), 0, 0));
+    }
+  };
+  auto stash_b = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      *reinterpret_cast<u32x4*>(bs + buf * CH + (i * kHiloWaves * 64 + threadIdx.x) * 8) = bst[i];
+  };
+
+  // A fragments of k step ks. A step at or past nks (the ring's refills during the last
+  // chunk) would read the next rows' bytes, real traffic that is thrown away: those loads
+  // take an empty resource instead (still issued, so the issue stays branch-free).
+  const __amdgpu_buffer_rsrc_t rz = make_rsrc(j.Xhi, 0);
+  auto load_a = [&](int ks, u32x4 (&ah)[MB], u32x4 (&al)[MB]) {
+    const bool live = ks < nks;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      ah[mb] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(live ? rh : rz, (int)(xoff[mb] + 64 * ks), 0, 0));
+      if (LO) al[mb] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(live ? rl : rz, (int)(xoff[mb] + 64 * ks), 0, 0));
+    }
+  };
+  // zero the elements of this lane's 8 columns 32 ks + 8 g .. that lie past p
+  auto mask_tail = [&](int ks, u32x4 (&ah)[MB], u32x4 (&al)[MB]) {
+    const int lim = p - (32 * ks + 8 * g);
+    u32x4 mk;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+      mk[d] = (2 * d < lim ? 0x0000FFFFu : 0u) | (2 * d + 1 < lim ? 0xFFFF0000u : 0u);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      ah[mb] &= mk;
+      if (LO) al[mb] &= mk;
+    }
+  };
+  // X fragments kFewSteps k steps ahead in a ring of kFewSteps register sets: set kk holds
+  // step ks = c kFewSteps + kk of chunk c and is reloaded with step ks + kFewSteps right after
+  // its MFMAs, so kFewSteps - 1 steps of loads stay in flight per wave while one is used.
+  // The ring index is static in the unrolled chunk, so no register is copied (a copy of a
+  // register a load has not yet filled would wait for that load).
+  u32x4 xh[kFewSteps][MB], xl[kFewSteps][MB];
+  fetch_b(0);
+  stash_b(0);
+#pragma unroll
+  for (int kk = 0; kk < kFewSteps; ++kk) load_a(kk, xh[kk], xl[kk]);
+  __syncthreads();
+  for (int c = 0; c < nch; ++c) {
+    fetch_b(c + 1);
+    const u16* bc = bs + (c & 1) * CH + lane * 8;
+#pragma unroll
+    for (int kk = 0; kk < kFewSteps; ++kk) {
+      const int ks = c * kFewSteps + kk;
+      if (ks == nks - 1 && (p & 31)) mask_tail(ks, xh[kk], xl[kk]);
+      bf16x8 bh[NB], bl[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const u16* f = bc + (kk * NB + nb) * 1024;
+        bh[nb] = as_frag(*reinterpret_cast<const u32x4*>(f));
+        bl[nb] = as_frag(*reinterpret_cast<const u32x4*>(f + 512));
+      }
+      if (ks < nks) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            acc[mb][nb] = mma(as_frag(xh[kk][mb]), bh[nb], acc[mb][nb]);
+            acc[mb][nb] = mma(as_frag(xh[kk][mb]), bl[nb], acc[mb][nb]);
+            if (LO) acc[mb][nb] = mma(as_frag(xl[kk][mb]), bh[nb], acc[mb][nb]);
+          }
+      }
+      load_a(ks + kFewSteps, xh[kk], xl[kk]);
+    }
+    stash_b((c + 1) & 1);
+    __syncthreads();
+  }
+
+  softmax_residuals<NB, GROUP>(j, 0, acc, ylab, lacc);
+}
+
 // Gradient partial X^T R of the 32 NW columns from c0 over rows [rbeg, rend) (rbeg a
 // multiple of 32), written to gp: element (column j, class kk of group q) at
 // gp[q cstride + j K + kk].
@@ -693,6 +827,22 @@ __global__ __launch_bounds__(kHiloWaves * 64) void hilo_logits(HiloArgs a) {
   }
 }
 
+template <int NB, bool LO>
+__global__ __launch_bounds__(kHiloWaves * 64) void hilo_logits_few(HiloArgs a) {
+  __shared__ double lsum[kHiloWaves];
+  __shared__ __attribute__((aligned(16))) u16 bs[few_lds_elems<NB>()];
+  double lacc[1] = {0.0};
+  logits_few_rows<NB, NB, LO>(job_of(a), lacc, bs);
+  const double v = wave_sum(lacc[0]);
+  if ((threadIdx.x & 63) == 0) lsum[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int i = 0; i < kHiloWaves; ++i) t += lsum[i];
+    a.lpart[0] = t;
+  }
+}
+
 // One workgroup of NW waves per (32 NW-column block, row slice) item, items slice-major (the
 // column blocks of a slice consecutive) in the XCD-aware order; the launch has xcd_span(items,
 // gcols) workgroups.
@@ -749,11 +899,12 @@ __global__ __launch_bounds__(256) void batch_pack(BatchArgs a) {
   }
 }
 
-template <int NB, int GROUP, bool LO>
+// FEW: every problem has few_rows rows at most (one item each).
+template <int NB, int GROUP, bool LO, bool FEW>
 __global__ __launch_bounds__(kHiloWaves * 64, 2) void batch_logits(BatchArgs a) {
   constexpr int NC = NB / GROUP;                  // chains
   __shared__ double lsum[kHiloWaves][NC];
-  __shared__ __attribute__((aligned(16))) u16 bs[logits_lds_elems<NB, LO>()];
+  __shared__ __attribute__((aligned(16))) u16 bs[FEW ? few_lds_elems<NB>() : logits_lds_elems<NB, LO>()];
   const int64_t total = a.first_logits[a.nprob];
   for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
     const int b = find_problem(a.first_logits, a.nprob, it);
@@ -763,7 +914,8 @@ __global__ __launch_bounds__(kHiloWaves * 64, 2) void batch_logits(BatchArgs a) 
 #pragma unroll
     for (int c = 0; c < NC; ++c) lacc[c] = 0.0;
     const Job j = job_of(P, nullptr);
-    if (hot_slice(uniform(P.slice0) + rb * kHiloRows / uniform(P.rps), uniform(P.hot))) logits_rows<NB, GROUP, LO, kKeep>(j, rb, lacc, bs);
+    if constexpr (FEW) logits_few_rows<NB, GROUP, LO>(j, lacc, bs);
+    else if (hot_slice(uniform(P.slice0) + rb * kHiloRows / uniform(P.rps), uniform(P.hot))) logits_rows<NB, GROUP, LO, kKeep>(j, rb, lacc, bs);
     else logits_rows<NB, GROUP, LO, kStream>(j, rb, lacc, bs);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -822,9 +974,10 @@ template hipError_t launch_split<float>(const float*, int64_t, int64_t, int64_t,
 template hipError_t launch_split<double>(const double*, int64_t, int64_t, int64_t, uint16_t*, uint16_t*, int64_t, hipStream_t);
 
 template <int NB, int GROUP, bool LO>
-static hipError_t launch_batch_t(const BatchArgs& a, int grad_waves, const int grid[3], bool pack, hipStream_t s) {
+static hipError_t launch_batch_t(const BatchArgs& a, bool few, int grad_waves, const int grid[3], bool pack, hipStream_t s) {
   if (pack) hipLaunchKernelGGL((batch_pack<NB, GROUP>), dim3(grid[0]), dim3(256), 0, s, a);
-  hipLaunchKernelGGL((batch_logits<NB, GROUP, LO>), dim3(grid[1]), dim3(kHiloWaves * 64), 0, s, a);
+  if (few) hipLaunchKernelGGL((batch_logits<NB, GROUP, LO, true>), dim3(grid[1]), dim3(kHiloWaves * 64), 0, s, a);
+  else hipLaunchKernelGGL((batch_logits<NB, GROUP, LO, false>), dim3(grid[1]), dim3(kHiloWaves * 64), 0, s, a);
   switch (grad_waves) {
     case 8: hipLaunchKernelGGL((batch_grad<NB, GROUP, LO, 8>), dim3(grid[2]), dim3(512), 0, s, a); break;
     case 4: hipLaunchKernelGGL((batch_grad<NB, GROUP, LO, 4>), dim3(grid[2]), dim3(256), 0, s, a); break;
@@ -835,11 +988,11 @@ static hipError_t launch_batch_t(const BatchArgs& a, int grad_waves, const int g
 }
 
 // chains x group class blocks (group = 16-class blocks per chain), at most 4 in all
-hipError_t launch_batch_pass(const BatchArgs& a, int chains, int group, bool lo, int grad_waves, const int grid[3], bool pack, hipStream_t s) {
+hipError_t launch_batch_pass(const BatchArgs& a, int chains, int group, bool lo, bool few, int grad_waves, const int grid[3], bool pack, hipStream_t s) {
 #define HMC_BATCH(C_, G_)                                                                 \
   if (chains == C_ && group == G_)                                                        \
-    return lo ? launch_batch_t<C_ * G_, G_, true>(a, grad_waves, grid, pack, s)                      \
-              : launch_batch_t<C_ * G_, G_, false>(a, grad_waves, grid, pack, s);
+    return lo ? launch_batch_t<C_ * G_, G_, true>(a, few, grad_waves, grid, pack, s)                      \
+              : launch_batch_t<C_ * G_, G_, false>(a, few, grad_waves, grid, pack, s);
   HMC_BATCH(1, 1) HMC_BATCH(2, 1) HMC_BATCH(4, 1) HMC_BATCH(1, 2) HMC_BATCH(2, 2) HMC_BATCH(1, 4)
 #undef HMC_BATCH
   return hipErrorInvalidValue;
@@ -851,7 +1004,8 @@ static hipError_t launch_hilo_t(const HiloArgs& a, int logits_wg, int grad_waves
   const int nks = (a.p + 31) / 32;
   const int packs = (nks * NB * 64 + 255) / 256;
   if (pack) hipLaunchKernelGGL(pack_b_kernel<NB>, dim3(packs), dim3(256), 0, s, a);
-  hipLaunchKernelGGL((hilo_logits<NB, LO>), dim3(logits_wg), dim3(kHiloWaves * 64), 0, s, a);
+  if (a.n <= few_rows(NB)) hipLaunchKernelGGL((hilo_logits_few<NB, LO>), dim3(1), dim3(kHiloWaves * 64), 0, s, a);
+  else hipLaunchKernelGGL((hilo_logits<NB, LO>), dim3(logits_wg), dim3(kHiloWaves * 64), 0, s, a);
   const int64_t span = xcd_span((int64_t)gcols * a.nsplit, gcols);
   if (grad_waves == 2) hipLaunchKernelGGL((hilo_grad<NB, LO, 2>), dim3((unsigned)span), dim3(128), 0, s, a, gcols);
   else if (grad_waves == 4) hipLaunchKernelGGL((hilo_grad<NB, LO, 4>), dim3((unsigned)span), dim3(256), 0, s, a, gcols);

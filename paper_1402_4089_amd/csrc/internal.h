@@ -131,6 +131,10 @@ constexpr int kHiloWaves = 4;      // waves per logits workgroup
 constexpr int kHiloMB = 2;         // 16-row M blocks per logits wave
 constexpr int kHiloRows = kHiloWaves * 16 * kHiloMB;   // rows per logits row block
 
+// Rows up to which a problem's logits take X straight to the matrix operand (logits_few_rows in
+// hilo.hip), with nb class blocks.
+constexpr int few_rows(int nb) { return nb == 4 ? kHiloRows : 80; }
+
 // XCD-aware order of the split-precision gradient items (hilo.hip): the launch order is
 // split into chunks of G consecutive items dealt round-robin to the kXcds XCDs; the launch
 // covers xcd_span(items, G) positions. grad_chunk is G for the batched kernel (the column
@@ -283,7 +287,7 @@ template <typename Tin>
 hipError_t launch_split(const Tin* X, int64_t ldx, int64_t n, int64_t p, uint16_t* hi, uint16_t* lo,
                         int64_t ldo, hipStream_t s);
 
-hipError_t launch_batch_pass(const BatchArgs& a, int chains, int group, bool lo, int grad_waves, const int grid[3], bool pack, hipStream_t s);
+hipError_t launch_batch_pass(const BatchArgs& a, int chains, int group, bool lo, bool few, int grad_waves, const int grid[3], bool pack, hipStream_t s);
 // grid: {start/accept, epilogue} workgroup counts
 hipError_t launch_batch_start(const BatchArgs& a, int grid, hipStream_t s);
 hipError_t launch_batch_epilogue(const BatchArgs& a, int grid, hipStream_t s);
