@@ -15,7 +15,8 @@
 // 4 + t, 8 + t, 12 + t (t = 0 .. 3) of block l, then of block l + 32, by fused multiply-adds; lanes
 // w and w + 16 are added, then w = 0 .. 15 in turn. log K thus keeps its bits but for the order of
 // the float64 sum over rows. So a lane loads whole blocks, 64 bytes in four loads; in float64,
-// where any order will do, neighbouring lanes load neighbouring pieces.
+// where any order will do, neighbouring lanes load neighbouring pieces. (The float64 probit link's
+// function leaves 40 bytes of a lane's state in scratch.)
 #include <math.h>
 
 #include "device_common.h"

@@ -141,8 +141,9 @@ template <typename T> __device__ __forceinline__ T tree16(const T (&e)[16]) {
 }
 
 // Most waves of a workgroup. The two coefficient groups, the accumulators and the float64 sums
-// of up to 9 classes (4 in float64) fit 256 registers per lane, so two waves per SIMD and
-// workgroups of 8 waves; more classes take the 512 of one wave per SIMD.
+// of up to 9 classes (4 in float64) take 256 registers per lane (9 in float32 and 20 bytes of
+// scratch), so two waves per SIMD and workgroups of 8 waves; more classes take the 512 of one wave
+// per SIMD (14, 15 and 16 in float64 and 88, 216 and 220 bytes of scratch).
 template <typename T, int F> constexpr int sample_waves() { return F <= (sizeof(T) == 4 ? 9 : 4) ? 8 : 4; }
 
 // K <= 16: F classes with coefficients (K, or K - 1 with the pinned class last); lane 16 g + c

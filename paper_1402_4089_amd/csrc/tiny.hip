@@ -17,6 +17,9 @@
 // turn) and its softmax with the same functions and tree, so log K does not depend on which
 // of the two runs but for the order of the float64 sum over rows; the gradient's row sums are
 // float64 here where that kernel adds 16 rows at a time in the state's precision.
+//
+// With 1024 threads a lane has 128 registers: in float64, one and eight padded classes keep 68 and
+// 92 bytes of scratch per lane.
 #include <math.h>
 
 #include "device_common.h"
@@ -301,11 +304,15 @@ hipError_t launch_one(const TinyArgs& a, size_t lds, hipStream_t s) {
 }  // namespace
 
 // Where one workgroup beats the general path's kernels. Both times are near linear, here in us as
-// measured at 400 sizes (f = padded free classes; p f <= 512 leaves a thread two gradient
+// measured in a graph at 400 sizes (f = padded free classes; p f <= 512 leaves a thread two gradient
 // shares at most, and beyond it both the time and its spread double); the rule asks for 10% less
 // per update and 5% less per gradient. Per update in FP32: p = 64 at n = 100, K = 3: 4.3 against
-// 6.6; p = 128: 7.6 against 6.7, not taken. Per gradient: p = 20 at n = 500, K = 3: 9.4 against
-// 9.2 in a graph and about 13 launched singly; p = 256 at n = 100, K = 1: 21.7 against 9.6, not taken.
+// 6.6; p = 128: 7.6 against 6.7, not taken. Per gradient: p = 20 at n = 500, K = 3, FP64: 9.7 against
+// 10.3 in a graph and 11.3 launched singly; p = 256 at n = 100, K = 1: 21.7 against 9.6, not taken.
+// A gradient launched singly is the faster one at every size taken, by 1 to 4 us of 10, since the
+// general path's three launches pace it. In a graph it is at seven in eight: the model is off for 10
+// or more classes in FP64 (n = 51, p = 2, K = 15: 8.9 against 8.1 in a graph, 9.0 against 10.2
+// singly) and for one class of some 50 columns (n = 204, p = 50, K = 2, FP32: 9.2 against 7.9).
 bool tiny_fits(int64_t n, int64_t p, int K, bool pin, bool f64, bool update) {
   if (n > 1024 || p > 256 || K > 16 || p * K > 1024 || n * p * K > (int64_t)1 << 16) return false;
   const int fp = class_pad(pin ? K - 1 : K);
